@@ -189,3 +189,29 @@ def test_teacher_forced_bf16_decode():
             zg = host(ctx.step(dev_i32(g[None])))[0]
     say(f"  worst logit error {worst:.2e}, margin-exempt steps {exempt}")
     assert exempt <= 2
+
+
+@pytest.mark.parametrize("V,B,G", [(1088, 1, 8), (12416, 3, 16), (12288, 2, 8), (65536, 1, 24)])
+def test_decide_statistics_of_stored_logits(V, B, G):
+    """The statistics kernel over stored logits at its three column tiles (128 with a partial last
+    tile and with whole tiles, 192, 256), on 16-byte aligned logits and on a view one float into a
+    buffer: both give the oracle's decision, and the same one."""
+    m = ModelShape(n_layers=1, d_model=64, n_heads=1, n_kv_heads=1, head_dim=64, d_ff=64, vocab=V, dtype="bf16")
+    ctx = make_ctx(m, model_weights(m, seed=1), B, 8, 8 * B, G)
+    ctx.refresh_prompt(dev_i32(np.zeros(8 * B, np.int32)), [8] * B, dev_i32(np.full((B, G), m.mask_id)))
+    rng = np.random.default_rng(V)
+    z = (rng.standard_normal((B, G, V)) * 1.3).astype(np.float32)
+    z[:, :, m.mask_id] = 40.0                        # MASK's own logit takes part in nothing
+    g = np.full((B, G), m.mask_id, np.int32)
+    g[:, ::3] = rng.integers(0, V - 1, (B, len(range(0, G, 3))))
+    buf = torch.empty(z.size + 1, dtype=torch.float32, device="cuda")
+    view = buf[1:].view(B, G, V)
+    view.copy_(dev_f32(z))
+    outs = [ctx.decide(t, dev_i32(g), k=2, tau=0.1) for t in (dev_f32(z), view)]
+    for b in range(B):
+        want = od.decide(z[b], g[b], m.mask_id, 2, 0.1)[0]
+        assert od.decision_margin(z[b], g[b], m.mask_id, 2, 0.1) > LSE_SLACK
+        for out in outs:
+            assert out[0][b].tolist() == want.tolist()
+    for x, y in zip(*outs):
+        assert bool((x == y).all())
