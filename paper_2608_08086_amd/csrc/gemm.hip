@@ -605,71 +605,119 @@ int launch_gemm_bf16(int epi, const GemmArgs& a, hipStream_t st) {
 }
 
 // ---------------------------------------------------------------------------
-// fp32 kernel: 64 x 64 tile, BK 16; thread (tx, ty) owns columns tx and
-// tx + 32 (a pair) of rows ty + 8 i.
-template <int EPI>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
-  constexpr int BM = 64, BN = 64, BK = 16;
-  __shared__ float As[BM][BK + 1];
-  __shared__ float Bs[BN][BK + 1];
-  const int tid = threadIdx.x, tx = tid & 31, ty = tid >> 5;
+// fp32 kernel.  KS waves share a tile of 16 RB rows x 16 CB columns and split K:
+// wave w takes the 16-wide k chunks w, w + KS, ... with v_mfma_f32_16x16x4_f32,
+// the fragments loaded straight from global memory (a lane's float4 holds four
+// consecutive k of one row; MFMA i of a chunk multiplies element i of every
+// lane, the same k on both sides) and PF chunks requested ahead.  The waves'
+// sums are added in wave order through LDS, then the epilogue runs.  The order
+// of a sum depends on K alone, so a row's result does not depend on the tile
+// or on the rows of the launch.
+// Small fp32 models are bound by the chain of global load latencies, so the
+// chunks of a row are spread over waves and requested together: 32 rows of the
+// tiny model take 5 us at K 256 and 11 us at K 1024, where one 16-wide
+// chunk loaded, staged and multiplied at a time took 23 and 85 us; 4096 x 12288
+// x 4096 take 4.97 ms (83 TFLOP/s), where 64 x 64 LDS tiles on the vector units
+// took 8.19 ms.
+constexpr int F32_KS = 8;
+template <int EPI, int RB, int CB, int PF>
+__global__ __launch_bounds__(64 * F32_KS) void gemm_f32_kernel(GemmArgs a) {
+  constexpr int BM = 16 * RB, BN = 16 * CB;
+  static_assert(CB % 2 == 0, "pair halves are whole column blocks");
+  __shared__ float red[F32_KS][CB * 4][64];
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lg = lane >> 4, lc = lane & 15;
   const int tile_n = blockIdx.x, m0 = blockIdx.y * BM;
-  const int lr = tid >> 2, lk = (tid & 3) * 4;
-  const float* A = (const float*)a.A;
-  const int arow = m0 + lr;
-  const bool aval = arow < a.M;
-  const float* asrc = A + (size_t)(aval ? arow : 0) * a.lda + lk;
-  bool second;
-  const int wr = brow_index<EPI, BN>(a, tile_n, lr, &second);
-  const float* bsrc = (const float*)(second ? a.W2 : a.W) + (size_t)wr * a.ldw + lk;
-  float acc0[8], acc1[8];
+  // rows past M load row M - 1; those output rows are never stored
+  const float* ap[RB];
+  const float* wp[CB];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) { acc0[i] = 0.f; acc1[i] = 0.f; }
-  for (int k0 = 0; k0 < a.K; k0 += BK) {
-    const float4 av = aval ? *(const float4*)(asrc + k0) : make_float4(0.f, 0.f, 0.f, 0.f);
-    const float4 bv = *(const float4*)(bsrc + k0);
-    As[lr][lk + 0] = av.x; As[lr][lk + 1] = av.y; As[lr][lk + 2] = av.z; As[lr][lk + 3] = av.w;
-    Bs[lr][lk + 0] = bv.x; Bs[lr][lk + 1] = bv.y; Bs[lr][lk + 2] = bv.z; Bs[lr][lk + 3] = bv.w;
-    __syncthreads();
+  for (int rb = 0; rb < RB; ++rb) ap[rb] = (const float*)a.A + (size_t)min(m0 + rb * 16 + lc, a.M - 1) * a.lda + lg * 4;
 #pragma unroll
-    for (int kk = 0; kk < BK; ++kk) {
-      const float b0 = Bs[tx][kk], b1 = Bs[tx + 32][kk];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const float av2 = As[ty + 8 * i][kk];
-        acc0[i] = fmaf(av2, b0, acc0[i]);
-        acc1[i] = fmaf(av2, b1, acc1[i]);
-      }
-    }
-    __syncthreads();
+  for (int cb = 0; cb < CB; ++cb) {
+    bool second;
+    const int wr = brow_index<EPI, BN>(a, tile_n, cb * 16 + lc, &second);
+    wp[cb] = (const float*)(second ? a.W2 : a.W) + (size_t)wr * a.ldw + lg * 4;
   }
+  f32x4 acc[RB][CB];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int row = m0 + ty + 8 * i;
-    if (row >= a.M) continue;
-    if constexpr (epi_paired(EPI)) {
-      epi_tile_pair<EPI, float, BN>(a, tile_n, tx, row, acc0[i], acc1[i]);
-    } else if constexpr (EPI == EPI_STORE) {
-      epi_store(a, row, tile_n * BN + tx, acc0[i]);
-      epi_store(a, row, tile_n * BN + tx + 32, acc1[i]);
-    } else {
-      epi_resid(a, row, tile_n * BN + tx, acc0[i]);
-      epi_resid(a, row, tile_n * BN + tx + 32, acc1[i]);
+  for (int i = 0; i < RB; ++i)
+#pragma unroll
+    for (int j = 0; j < CB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int nch = a.K / 16;
+  for (int c0 = w; c0 < nch; c0 += F32_KS * PF) {
+    f32x4 fa[PF][RB], fw[PF][CB];
+#pragma unroll
+    for (int u = 0; u < PF; ++u) {
+      const int k0 = min(c0 + u * F32_KS, nch - 1) * 16;   // past the last chunk: loaded, not multiplied
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) fa[u][rb] = *(const f32x4*)(ap[rb] + k0);
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) fw[u][cb] = *(const f32x4*)(wp[cb] + k0);
+    }
+#pragma unroll
+    for (int u = 0; u < PF; ++u) {
+      if (c0 + u * F32_KS >= nch) break;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+          for (int cb = 0; cb < CB; ++cb)
+            acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[u][rb][i], fw[u][cb][i], acc[rb][cb], 0, 0, 0);
+    }
+  }
+  // accumulator (rb, cb)[i]: row 16 rb + 4 lg + i, tile column 16 cb + lc; wave i < 4 finishes rows 4 lg + i
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    if (rb) __syncthreads();
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) red[w][cb * 4 + i][lane] = acc[rb][cb][i];
+    __syncthreads();
+    const int row = m0 + rb * 16 + lg * 4 + w;
+    if (w < 4 && row < a.M) {
+      float v[CB];
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) {
+        v[cb] = red[0][cb * 4 + w][lane];
+#pragma unroll
+        for (int s = 1; s < F32_KS; ++s) v[cb] += red[s][cb * 4 + w][lane];
+      }
+      if constexpr (epi_paired(EPI)) {
+#pragma unroll
+        for (int cb = 0; cb < CB / 2; ++cb)
+          epi_tile_pair<EPI, float, BN>(a, tile_n, cb * 16 + lc, row, v[cb], v[cb + CB / 2]);
+      } else {
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+          const int col = tile_n * BN + cb * 16 + lc;
+          if constexpr (EPI == EPI_STORE) epi_store(a, row, col, v[cb]);
+          else epi_resid(a, row, col, v[cb]);
+        }
+      }
     }
   }
 }
 
+template <int EPI>
+static void run_f32(const GemmArgs& a, hipStream_t st) {
+  // 64 x 64 tiles (half the loads per product) once they fill the GPU, 32 x 32 below
+  const long big = (long)(a.N / 64) * ((a.M + 63) / 64);
+  if (big >= 256) gemm_f32_kernel<EPI, 4, 4, 2><<<dim3(a.N / 64, (a.M + 63) / 64), 64 * F32_KS, 0, st>>>(a);
+  else gemm_f32_kernel<EPI, 2, 2, 4><<<dim3(a.N / 32, (a.M + 31) / 32), 64 * F32_KS, 0, st>>>(a);
+}
+
 int launch_gemm_f32(int epi, const GemmArgs& a, hipStream_t st) {
-  constexpr int BM = 64, BN = 64;
   if (!gemm_args_ok(epi, a)) return 1;
-  if (a.M <= 0 || a.N % BN || a.K % 16) return 1;
-  if (epi == EPI_QKV && (a.hd % BN)) return 1;
-  dim3 grid(a.N / BN, (a.M + BM - 1) / BM);
+  if (a.M <= 0 || a.N % 64 || a.K % 16) return 1;
+  if (epi == EPI_QKV && (a.hd % 64)) return 1;
   switch (epi) {
-    case EPI_STORE: gemm_f32_kernel<EPI_STORE><<<grid, 256, 0, st>>>(a); break;
-    case EPI_RESID: gemm_f32_kernel<EPI_RESID><<<grid, 256, 0, st>>>(a); break;
-    case EPI_SWIGLU: gemm_f32_kernel<EPI_SWIGLU><<<grid, 256, 0, st>>>(a); break;
-    case EPI_QKV: gemm_f32_kernel<EPI_QKV><<<grid, 256, 0, st>>>(a); break;
+    case EPI_STORE: run_f32<EPI_STORE>(a, st); break;
+    case EPI_RESID: run_f32<EPI_RESID>(a, st); break;
+    case EPI_SWIGLU: run_f32<EPI_SWIGLU>(a, st); break;
+    case EPI_QKV: run_f32<EPI_QKV>(a, st); break;
     default: return 1;
   }
   return 0;

@@ -38,6 +38,25 @@ def test_gemm_f32_matches_oracle(M, N, K):
     np.testing.assert_allclose(Y, on.linear(A64, W64), rtol=0, atol=1e-4)
 
 
+@pytest.mark.parametrize("M,N,K", [
+    (1, 64, 64),          # one row; fewer 16-wide chunks than waves
+    (33, 64, 192),        # 32-row tiles with one row over, chunks not a multiple of the waves
+    (31, 1024, 1088),     # the last batch of chunks partly past K
+    (1025, 1024, 320),    # 64 x 64 tiles (272 of them), one row over
+])
+def test_gemm_f32_tiles_match_oracle(M, N, K):
+    say(f"gemm fp32 tiles M={M} N={N} K={K}")
+    a = archer()
+    A, A64 = rand_f32((M, K), 16, 1)
+    W, W64 = rand_f32((N, K), 16, 2)
+    Y = host(a.op_gemm(A, W, a.FP32))
+    # K roundings of partial sums of size <= sqrt(K) at 2^-24 each, as a random walk: ~ K 2^-24; 4x that
+    np.testing.assert_allclose(Y, on.linear(A64, W64), rtol=0, atol=4 * K * 2.0**-24 + 1e-6)
+    # a row's sums do not depend on the tile: the first rows alone (32 x 32 tiles) give the same bits
+    n = min(M, 5)
+    np.testing.assert_array_equal(host(a.op_gemm(A[:n].contiguous(), W, a.FP32)), Y[:n])
+
+
 @pytest.mark.parametrize("M,N,K", [(37, 192, 320), (256, 512, 4096), (300, 65536, 256), (3900, 4096, 256),
                                    (2600, 4608, 192)])
 def test_gemm_two_term_activation_matches_oracle(M, N, K):
