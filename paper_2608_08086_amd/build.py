@@ -28,12 +28,14 @@ FLAGS = [
     "-std=c++17", "-O3", "-fPIC", f"--offload-arch={ARCH}",
     # packed-fp32 instructions are disabled for every kernel
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    # MFMA results in ordinary VGPRs: the softmax and epilogues read them
-    # without accumulator-register copies
-    "-mllvm", "-amdgpu-mfma-vgpr-form",
     "-Wall", "-Wno-unused-function", "-Wno-unused-variable",
     f"-I{INCLUDE}", f"-I{CSRC}",
 ]
+# MFMA results in ordinary VGPRs: the softmax and epilogues read them without
+# accumulator-register copies
+VGPR_FORM = ["-mllvm", "-amdgpu-mfma-vgpr-form"]
+# sources whose accumulators fill the accumulation registers instead
+AGPR_SOURCES = {"gemm_wide.hip"}
 
 
 def sources() -> list[str]:
@@ -42,7 +44,8 @@ def sources() -> list[str]:
 
 def _compile(src: str) -> str:
     obj = os.path.join(BUILD, os.path.basename(src) + ".o")
-    cmd = [HIPCC, *FLAGS, "-c", src, "-o", obj]
+    form = [] if os.path.basename(src) in AGPR_SOURCES else VGPR_FORM
+    cmd = [HIPCC, *FLAGS, *form, "-c", src, "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     out = "\n".join(l for l in (r.stdout + r.stderr).splitlines()
                     if "packed-fp32-ops" not in l)

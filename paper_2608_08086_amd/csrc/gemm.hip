@@ -489,44 +489,59 @@ int gemm_ksplit(int N, int K, int rows) {
   return S;
 }
 
+// Time of one round of a one-slice launch's tiles (256 workgroups, one per CU)
+// in us at K 4096, measured on the LLaDA-8B projections with full rounds (the
+// ragged batch's 4096- and 24853-row passes; 768- and 4352-row passes order the
+// same way).  Two-term bf16 and single-term fp16 launches; 0: not a
+// configuration of the kind.
+static double tile_round_us(int cfg, bool f16) {
+  switch (cfg) {
+    case GEMM_NCFG + 1: return f16 ? 37.0 : 53.0;      // 128 x 128
+    case GEMM_NCFG + 0: return f16 ? 0.0 : 79.5;       // 128 x 192
+    case GEMM_NCFG + 2: return f16 ? 0.0 : 93.5;       // 128 x 256
+    case GEMM_WIDE_128x192: return f16 ? 45.0 : 0.0;
+    case GEMM_WIDE_256x192: return f16 ? 75.0 : 140.0;
+    case GEMM_WIDE_256x256: return f16 ? 98.5 : 180.0;
+    default: return 0.0;
+  }
+}
+
+static void tile_size(int cfg, int* bm, int* bn) {
+  *bm = cfg == GEMM_WIDE_256x256 || cfg == GEMM_WIDE_256x192 ? 256 : 128;
+  *bn = cfg == GEMM_WIDE_256x256 || cfg == GEMM_NCFG + 2 ? 256 : cfg == GEMM_NCFG + 1 ? 128 : 192;
+}
+
+static bool one_slice_ok(int cfg, const GemmArgs& a, int epi) {
+  return cfg >= GEMM_NCFG + GEMM_NCFG_LDS ? gemm_wide_ok(cfg, a, epi) : gemm_lds_cfg_ok(cfg - GEMM_NCFG, a);
+}
+
 int gemm_pick_cfg(const GemmArgs& a, int epi) {
-  // The warp-specialised direct-to-LDS kernel (gemm_lds.hip).  Two-term
-  // launches of one K slice take the tile (128 x 256: 64 x 128 wave tiles,
-  // fewer LDS bytes per MFMA; 128 x 192; 128 x 128) with the fewest rounds of
-  // 256 workgroups (one per CU) times the time of a tile: measured on the
-  // LLaDA-8B projections, a 128 x 192 tile takes 1.5x and a 128 x 256 tile
-  // 1.77x the time of a 128 x 128 tile (so, for example, 256-row gate/up
-  // passes take 128 x 192 tiles, one round, and 256-row QKV passes 128 x 128
-  // tiles).  The LM head decides on N alone, so that the column tile of its
-  // fused decision statistics does not depend on the row count of a pass.
+  // One K slice with two-term or fp16 operands: the tile with the least rounds of 256 workgroups
+  // times the time of a round; of two within 2 % the wider one (so, for example,
+  // 256-row gate/up passes take 128 x 192 tiles, one round, 256-row QKV passes
+  // 128 x 128 tiles, and the 4096 rows of a serving batch 256 x 256 ones
+  // throughout).  The LM head takes the column tile by N alone (256, when N has
+  // at least 256 of them), so that the partials of its fused decision statistics
+  // do not depend on the row count of a pass.
   // Split-K launches take 128 x 192 tiles when N is a multiple of 192, else
   // 128 x 128; the 128 x 192 tile is not used for slices folded in one
   // workgroup (its second accumulator set does not fit the registers of two
   // waves per SIMD).
-  // Single-term fp16 launches (gate/up) choose the same way with their own
-  // tile times: 1.34x (128 x 192) and 1.66x (128 x 256) that of a 128 x 128
-  // tile, measured on the LLaDA-8B gate/up shape at 24853 rows.
-  const bool wide = (a.A2 || a.f16) && a.ksplit == 1;
-  const double t192 = a.f16 ? 1.34 : 1.5, t256 = a.f16 ? 1.66 : 1.77;
-  if (wide && epi == EPI_STORE) {
-    if (a.N % 256 == 0 && a.N / 256 >= 256 && gemm_lds_cfg_ok(2, a)) return GEMM_NCFG + 2;
-  } else if (wide) {
-    // the tile with the fewest rounds times tile time; a narrower tile must
-    // be 5 % cheaper than a wider one to be taken
-    const long mt = (a.M + 127) / 128;
-    const auto cost = [&](int bn, double t) { return (double)((a.N / bn * mt + 255) / 256) * t; };
+  const bool head = epi == EPI_STORE;
+  if ((a.A2 || a.f16) && a.ksplit == 1 && (!head || (a.N % 256 == 0 && a.N / 256 >= 256))) {
     int best = -1;
     double bc = 0;
-    if (a.N % 256 == 0 && gemm_lds_cfg_ok(2, a)) { best = 2; bc = cost(256, t256); }
-    if (a.N % 192 == 0 && gemm_lds_cfg_ok(0, a) && (best < 0 || cost(192, t192) < 0.95 * bc)) {
-      best = 0;
-      bc = cost(192, t192);
+    for (int cfg : {(int)GEMM_WIDE_256x256, (int)GEMM_WIDE_256x192, GEMM_NCFG + 2, (int)GEMM_WIDE_128x192, GEMM_NCFG + 0,
+                    GEMM_NCFG + 1}) {
+      const double t = tile_round_us(cfg, a.f16 != 0);
+      int bm, bn;
+      tile_size(cfg, &bm, &bn);
+      if (t == 0.0 || (head && bn != 256) || !one_slice_ok(cfg, a, epi)) continue;
+      const long wgs = (long)(a.N / bn) * ((a.M + bm - 1) / bm);
+      const double c = (double)((wgs + 255) / 256) * t;
+      if (best < 0 || c < 0.98 * bc) { best = cfg; bc = c; }
     }
-    if (a.N % 128 == 0 && gemm_lds_cfg_ok(1, a) && (best < 0 || cost(128, 1.0) < 0.95 * bc)) {
-      best = 1;
-      bc = cost(128, 1.0);
-    }
-    if (best >= 0) return GEMM_NCFG + best;
+    if (best >= 0) return best;
   }
   if (a.N % 192 == 0 && gemm_lds_cfg_ok(0, a)) {
     const bool fold = a.ksplit > 1 && !(a.part && gemm_partial_wanted(GEMM_NCFG + 0, a));
@@ -579,6 +594,7 @@ bool gemm_args_ok(int epi, const GemmArgs& a) {
 
 int launch_gemm_bf16_cfg(int epi, int cfg, bool partial, const GemmArgs& a, hipStream_t st) {
   if (!gemm_args_ok(epi, a)) return 1;
+  if (cfg >= GEMM_NCFG + GEMM_NCFG_LDS) return partial ? 1 : launch_gemm_wide(epi, cfg, a, st);
   if (cfg >= GEMM_NCFG) return launch_gemm_lds_cfg(epi, cfg - GEMM_NCFG, partial, a, st);
   if (a.f16 || !gemm_cfg_ok(cfg, a, epi)) return 1;   // the register-staged kernel is bf16 only
   if (partial && (!a.part || a.ksplit < 2)) return 1;

@@ -60,7 +60,8 @@ __device__ __forceinline__ void epi_swiglu(const GemmArgs& a, int row, int f, fl
 // RoPE of one (first-half, second-half) dimension pair by (cos, sin); the
 // single definition used by every epilogue that rotates q/k.
 __device__ __forceinline__ float2 rope_rotate(float v1, float v2, float2 cs) {
-  return make_float2(v1 * cs.x - v2 * cs.y, v2 * cs.x + v1 * cs.y);
+  // fused explicitly: the same bits in every kernel, whatever the compiler contracts
+  return make_float2(fmaf(v1, cs.x, -(v2 * cs.y)), fmaf(v2, cs.x, v1 * cs.y));
 }
 
 // head in [0, hq + 2 hkv): q heads, k heads, v heads; v1 / v2 = dims j, j + hd/2
@@ -118,13 +119,19 @@ __device__ __forceinline__ void epi_store4(const GemmArgs& a, int row, int col, 
   }
 }
 
-__device__ __forceinline__ void epi_resid4(const GemmArgs& a, int row, int col, f32x4 v) {
+__device__ __forceinline__ f32x4 epi_resid_read4(const GemmArgs& a, int row, int col) {
+  const float* p = a.X + (size_t)row * a.ldx + col;
+  if (((a.ldx & 3) | ((uintptr_t)a.X & 15)) == 0) return *(const f32x4*)p;
+  return f32x4{p[0], p[1], p[2], p[3]};
+}
+
+__device__ __forceinline__ void epi_resid_write4(const GemmArgs& a, int row, int col, f32x4 v) {
   float* p = a.X + (size_t)row * a.ldx + col;
   if (((a.ldx & 3) | ((uintptr_t)a.X & 15)) == 0) {
-    *(f32x4*)p += v;
+    *(f32x4*)p = v;
   } else {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) p[e] += v[e];
+    for (int e = 0; e < 4; ++e) p[e] = v[e];
   }
 }
 

@@ -34,122 +34,9 @@
 // same split-K slices and the same epilogues.  fp16 operands run only here.
 #include <algorithm>
 
-#include "gemm_common.h"
-
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+#include "gemm_tile.h"
 
 namespace {
-
-// s_waitcnt immediates (gfx9 encoding)
-#define GL_VMCNT(n) (((n) & 15) | (7 << 4) | (15 << 8) | ((((n) >> 4) & 3) << 14))
-#define GL_LGKMCNT0 (15 | (7 << 4) | (0 << 8) | (3 << 14))
-
-// M0 is listed as clobbered; no other code of this file keeps a value in it.
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void gl_dma16(const void* sbase, unsigned voff, unsigned lds) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-               :
-               : "v"(voff), "s"(sbase), "s"(lds)
-               : "memory", "m0");
-}
-#pragma clang diagnostic pop
-
-__device__ __forceinline__ void gl_barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
-// Chunk swizzle of a 64-byte row (four 16-byte chunks), chosen by measurement
-// (LDS bank-conflict counter of ds_read_b128 over 16 rows x one chunk): the
-// chunk index is XORed with (row / 2) mod 4.
-__device__ __forceinline__ int gl_swz(int row) { return (row >> 1) & 3; }
-
-constexpr int BK = 32;      // k chunk per tile (one MFMA k step)
-constexpr int CPR = BK / 8; // 16-byte chunks per tile row
-
-// QKV projection, value heads.  A tile whose column pairs are all value pairs
-// is staged in LDS as the transposed tile (one row of BM + 8 keys per value
-// dimension) and written to V^T in 16-byte chunks along the key axis wherever
-// eight consecutive pass rows go to eight consecutive, aligned key columns of
-// one buffer; element stores otherwise.  Written one element per lane, the
-// transposed layout gives every two-byte store its own cache line, which the
-// L2 then reads whole to merge.  The stored values are those of
-// epi_tile_pair4.
-template <int BN>
-__device__ __forceinline__ bool qkv_value_tile(const GemmArgs& a, int tile_n) {
-  return tile_n * (BN / 2) >= (a.hq + a.hkv) * (a.hd / 2);
-}
-constexpr int VT_PAD = 8;
-template <int BM, int BN, int NTHREADS>
-__device__ __forceinline__ void store_value_tile(const GemmArgs& a, const f16* vs, int tile_n, int m0, int t) {
-  constexpr int KS = BM + VT_PAD, KC = BM / 8;
-  static_assert(NTHREADS % KC == 0, "a thread keeps one key chunk");
-  // this thread's chunk of eight keys is the same for every dimension row it stores
-  const int kc = t % KC, k0 = m0 + kc * 8;
-  if (k0 >= a.M) return;
-  const int nk = min(8, a.M - k0);
-  const int dst0 = a.row_dst[k0];
-  const bool fresh = dst_is_fresh(dst0);
-  const int col0 = fresh ? dst0 : dst_cache_row(dst0);
-  f16* vt = (f16*)(fresh ? a.Vtf : a.Vtc);
-  const int ld = fresh ? a.ldfresh : a.ldcache;
-  bool vec = nk == 8 && col0 % 8 == 0 && ld % 8 == 0 && ((uintptr_t)vt & 15) == 0;
-  for (int i = 1; i < 8 && vec; ++i) {
-    const int di = a.row_dst[k0 + i];
-    vec = dst_is_fresh(di) == fresh && (fresh ? di : dst_cache_row(di)) == col0 + i;
-  }
-  const int half = a.hd / 2, p0 = tile_n * (BN / 2);
-  for (int drow = t / KC; drow < BN; drow += NTHREADS / KC) {
-    const int p = p0 + (drow >> 1);
-    const int vh = p / half - a.hq - a.hkv, d = p % half + (drow & 1) * half;
-    const f16* src = vs + drow * KS + kc * 8;
-    if (vec) {
-      *(u32x4*)(vt + (size_t)(vh * a.hd + d) * ld + col0) = *(const u32x4*)src;
-    } else {
-      for (int i = 0; i < nk; ++i) {
-        const int di = a.row_dst[k0 + i];
-        if (dst_is_fresh(di)) ((f16*)a.Vtf)[(size_t)(vh * a.hd + d) * a.ldfresh + di] = src[i];
-        else ((f16*)a.Vtc)[(size_t)(vh * a.hd + d) * a.ldcache + dst_cache_row(di)] = src[i];
-      }
-    }
-  }
-}
-
-// QKV projection, query and key heads.  A tile whose column pairs are whole
-// query or key heads is staged in LDS as rotated rows (the values of
-// epi_tile_pair4) and written with 16-byte stores along each head's
-// dimensions, so every store covers whole 128-byte lines.  Written straight
-// from the accumulators, a store covers 32 bytes of each of 16 rows, and the
-// L2 reads every partly written line from memory first: the query and key
-// stores of a 4096-row pass fetched 0.5 GB for 67 MB of output.
-template <int BN>
-__device__ __forceinline__ bool qkv_qk_tile(const GemmArgs& a, int tile_n) {
-  const int half = a.hd / 2;
-  return (BN / 2) % half == 0 && (tile_n + 1) * (BN / 2) <= (a.hq + a.hkv) * half &&
-         (((uintptr_t)a.Qb | (uintptr_t)a.Kf | (uintptr_t)a.Kc) & 15) == 0;
-}
-constexpr int QK_PAD = 8;
-template <int BM, int BN, int NTHREADS>
-__device__ __forceinline__ void store_qk_tile(const GemmArgs& a, const f16* qs, int tile_n, int m0, int t) {
-  constexpr int RS = BN + QK_PAD, CH = BN / 8;   // staged row stride, 16-byte chunks per row
-  const int hd = a.hd, h0 = tile_n * (BN / hd);
-  for (int i = t; i < BM * CH; i += NTHREADS) {
-    const int r = i / CH, ch = i % CH, row = m0 + r;
-    if (row >= a.M) break;                        // i only grows, and so does row
-    const int head = h0 + ch * 8 / hd, d = ch * 8 % hd;
-    f16* p;
-    if (head < a.hq) {
-      p = (f16*)a.Qb + ((size_t)head * a.ldq + row) * hd;
-    } else {
-      const int dst = a.row_dst[row];
-      p = dst_is_fresh(dst) ? (f16*)a.Kf + ((size_t)(head - a.hq) * a.ldfresh + dst) * hd
-                            : (f16*)a.Kc + ((size_t)(head - a.hq) * a.ldcache + dst_cache_row(dst)) * hd;
-    }
-    *(u32x4*)(p + d) = *(const u32x4*)(qs + r * RS + ch * 8);
-  }
-}
 
 template <int BM, int BN, int WGM, int WGN, int NST, int EPI, bool SPLIT, int MODE, bool F16 = false>
 __global__ __launch_bounds__(512, 1) void gemm_lds_kernel(GemmArgs a) {
@@ -332,9 +219,8 @@ __global__ __launch_bounds__(512, 1) void gemm_lds_kernel(GemmArgs a) {
   // weight blocks of tile g run before X_g, those of the second half after
   // it.  After X_g the weight fragments of the first half are refilled with
   // those of tile g + 1 at once, each of the second half as soon as its
-  // block's MFMAs have taken it (one weight fragment set, so that 64 x 128
-  // wave tiles fit the registers), and the activation fragments of tile
-  // g + 1 go to the second set in among them.
+  // block's MFMAs have taken it, and the activation fragments of tile g + 1 go
+  // to the second set in among them.
   constexpr bool PIPE1 = NA == 1 && !FOLD;
   auto mfma_blocks = [&](int buf, int cb0, int cb1) {
 #pragma unroll
@@ -392,53 +278,8 @@ __global__ __launch_bounds__(512, 1) void gemm_lds_kernel(GemmArgs a) {
       }
     }
   };
-  // 64 x 128 wave tiles (8 weight blocks) keep one activation fragment set
-  // too: the last block's MFMAs take the activation fragments one by one and
-  // each is refilled right after, and the next tile starts with the MFMAs of
-  // the first activation fragment over its first half of blocks.
-  constexpr bool FA1 = PIPE1 && CB == 8;
   auto tile_p1 = [&](int g, int cur, bool more) {
-    if constexpr (FA1) {
-      constexpr int H = CB / 2;
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-        for (int cb = 0; cb < H; ++cb) acc[rb][cb] = mm(fb[0][cb], fa[0][0][rb], acc[rb][cb]);
-      if (more) {
-        __builtin_amdgcn_s_waitcnt(GL_LGKMCNT0);   // this wave's reads of tile g are done
-        gl_barrier();                               // X_g
-        const char* stn = smem + ((g + 1) % NST) * STAGE;
-#pragma unroll
-        for (int cb = 0; cb < H; ++cb) fb[0][cb] = *(const bf16x8*)(stn + b_lo[cb]);
-#pragma unroll
-        for (int cb = H; cb < CB - 1; ++cb) {
-#pragma unroll
-          for (int rb = 0; rb < RB; ++rb) acc[rb][cb] = mm(fb[0][cb], fa[0][0][rb], acc[rb][cb]);
-          fb[0][cb] = *(const bf16x8*)(stn + b_lo[cb]);
-        }
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-          acc[rb][CB - 1] = mm(fb[0][CB - 1], fa[0][0][rb], acc[rb][CB - 1]);
-          fa[0][0][rb] = *(const bf16x8*)(stn + a_lo[rb]);
-        }
-        fb[0][CB - 1] = *(const bf16x8*)(stn + b_lo[CB - 1]);
-        __builtin_amdgcn_sched_group_barrier(0x100, H, 0);   // the first half's weight fragments
-#pragma unroll
-        for (int cb = H; cb < CB - 1; ++cb) {
-          __builtin_amdgcn_sched_group_barrier(0x008, RB, 0);   // the MFMAs of block cb
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);    // its weight fragment
-        }
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);    // last block, activation fragment rb
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);    // its refill
-        }
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);      // the last weight fragment
-        __builtin_amdgcn_sched_barrier(0);
-      } else {
-        mfma_blocks(0, H, CB);
-      }
-    } else if constexpr (PIPE1) {
+    if constexpr (PIPE1) {
       constexpr int H = CB / 2, NB2 = CB - H;
       mfma_blocks(cur, 0, H);
       if (more) {
@@ -552,139 +393,12 @@ __global__ __launch_bounds__(512, 1) void gemm_lds_kernel(GemmArgs a) {
     }
     return;
   }
-  // accumulator (rb, cb)[e]: row wm*WM + 16*rb + lc, tile column tb[cb] + e,
-  // tb[cb] = tc[cb] - lc + 4*lg (tc evaluated at lane lc = 4*lg)
-  if constexpr (EPI == EPI_QKV && MODE == 0 && SPLIT) {
-    if (qkv_value_tile<BN>(a, tile_n)) {
-      constexpr int KS = BM + VT_PAD;
-      static_assert(BN * KS * 2 <= NST * STAGE, "the staged value tile fits the LDS stages");
-      f16* vs = (f16*)smem;
-      __syncthreads();   // X_v1
-      // tile column c < BN / 2 is pair c (first dimension half), c + BN / 2 its partner
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) {
-        const int kl = wm * WM + rb * 16 + lc;
-#pragma unroll
-        for (int cb = 0; cb < CB / 2; ++cb)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int c = tc[cb] - lc + 4 * lg + e;
-            vs[(2 * c) * KS + kl] = from_f32<f16>(acc[rb][cb][e]);
-            vs[(2 * c + 1) * KS + kl] = from_f32<f16>(acc[rb][cb + CB / 2][e]);
-          }
-      }
-      __syncthreads();   // X_v2
-      store_value_tile<BM, BN, 512>(a, vs, tile_n, m0, tid);
-      return;
-    }
-    if (qkv_qk_tile<BN>(a, tile_n)) {
-      constexpr int RS = BN + QK_PAD;
-      static_assert(BM * RS * 2 <= NST * STAGE, "the staged query / key tile fits the LDS stages");
-      f16* qs = (f16*)smem;
-      const int half = a.hd / 2;
-      __syncthreads();   // X_q1: every load landed, every fragment read done
-      // pair c < BN / 2 of the tile: head c / half of the tile, dimensions j and j + half
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) {
-        const int r = wm * WM + rb * 16 + lc, row = m0 + r;
-        if (row >= a.M) continue;
-        const float2* cs = a.rope + (size_t)a.row_pos[row] * half;
-#pragma unroll
-        for (int cb = 0; cb < CB / 2; ++cb) {
-          const int c = tc[cb] - lc + 4 * lg, j = c % half;
-          f16* q = qs + r * RS + (c / half) * a.hd + j;
-          f16x4 o1, o2;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float2 o = rope_rotate(acc[rb][cb][e], acc[rb][cb + CB / 2][e], cs[j + e]);
-            o1[e] = from_f32<f16>(o.x);
-            o2[e] = from_f32<f16>(o.y);
-          }
-          *(f16x4*)q = o1;
-          *(f16x4*)(q + half) = o2;
-        }
-      }
-      __syncthreads();   // X_q2
-      store_qk_tile<BM, BN, 512>(a, qs, tile_n, m0, tid);
-      return;
-    }
-  }
-  if constexpr (EPI == EPI_STORE && !FOLD && WGN == 2) {
-    // decision statistics partial (tile tile_n, wave half wn) of each row, from
-    // the fp32 results (the values the logits store would write); columns
-    // tb[cb] + e are stat_col(BN, wn, lg, cb, e).  All lanes take part in the
-    // shuffles; rows past M (clamped loads) are computed and not written.
-    if (a.tstat) {
-      const int np = 2 * (a.N / BN);
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) {
-        const int row = m0 + wm * WM + rb * 16 + lc;
-        const int rowc = min(row, a.M - 1);
-        const int orow = a.out_row ? a.out_row[rowc] : rowc;
-        const int cur = a.tg[orow];
-        float mx = -INFINITY;
-        int ix = 0x7fffffff;
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int col = tile_n * BN + tc[cb] - lc + 4 * lg + e;
-            const float v = acc[rb][cb][e];
-            if (col != a.mask_id && (v > mx || (v == mx && col < ix))) { mx = v; ix = col; }
-          }
-#pragma unroll
-        for (int o = 16; o <= 32; o <<= 1) {
-          const float m2 = __shfl_xor(mx, o, 64);
-          const int i2 = __shfl_xor(ix, o, 64);
-          if (m2 > mx || (m2 == mx && i2 < ix)) { mx = m2; ix = i2; }
-        }
-        float sum = 0.f;
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int col = tile_n * BN + tc[cb] - lc + 4 * lg + e;
-            const float v = acc[rb][cb][e];
-            if (col != a.mask_id) sum += stat_exp(v, mx);
-            if (col == cur && row < a.M) a.zg[orow] = v;
-          }
-        sum += __shfl_xor(sum, 16, 64);   // (s0 + s1), (s2 + s3)
-        sum += __shfl_xor(sum, 32, 64);   // (s0 + s1) + (s2 + s3)
-        if (lg == 0 && row < a.M) {
-          const size_t pi = (size_t)orow * np + 2 * tile_n + wn;
-          a.tstat[pi] = make_float2(mx, sum);
-          a.targ[pi] = ix;
-        }
-      }
-      if (!a.C) return;
-    }
-  }
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb) {
-    const int row = m0 + wm * WM + rb * 16 + lc;
-    if (row >= a.M) continue;
-    int tb[CB];
-#pragma unroll
-    for (int cb = 0; cb < CB; ++cb) tb[cb] = tc[cb] - lc + 4 * lg;
-    if constexpr (epi_paired(EPI)) {
-#pragma unroll
-      for (int cb = 0; cb < CB / 2; ++cb) {
-        const f32x4 v1 = FOLD ? tot[rb % (FOLD ? RB : 1)][cb % (FOLD ? CB : 1)] : acc[rb][cb];
-        const f32x4 v2 = FOLD ? tot[rb % (FOLD ? RB : 1)][(cb + CB / 2) % (FOLD ? CB : 1)] : acc[rb][cb + CB / 2];
-        epi_tile_pair4<EPI, bf16, BN>(a, tile_n, tb[cb], row, v1, v2);
-      }
-    } else {
-#pragma unroll
-      for (int cb = 0; cb < CB; ++cb) {
-        const int col = tile_n * BN + tb[cb];
-        const f32x4 v = FOLD ? tot[rb % (FOLD ? RB : 1)][cb % (FOLD ? CB : 1)] : acc[rb][cb];
-        if constexpr (EPI == EPI_STORE) epi_store4(a, row, col, v);
-        else epi_resid4(a, row, col, v);
-      }
-    }
-  }
+  constexpr bool STAGED = EPI == EPI_QKV && MODE == 0 && SPLIT, STATS = EPI == EPI_STORE && !FOLD && WGN == 2;
+  if constexpr (FOLD)
+    tile_epilogue<BM, BN, WGN, RB, CB, EPI, STAGED, STATS, NST * STAGE, 512>(a, smem, tile_n, m0, wm, wn, lane, tid, tc, tot);
+  else
+    tile_epilogue<BM, BN, WGN, RB, CB, EPI, STAGED, STATS, NST * STAGE, 512>(a, smem, tile_n, m0, wm, wn, lane, tid, tc, acc);
 }
-
 
 template <int BM, int BN, int WGM, int WGN, int NST, int EPI, int MODE>
 void lds_mode(const GemmArgs& a, int grid, hipStream_t st) {
@@ -715,7 +429,7 @@ struct LdsCfg { int BM, BN; };
 const LdsCfg kLds[GEMM_NCFG_LDS] = {
     {128, 192},   // 0: 2 x 2 multiply waves of 64 x 96, 4 stages
     {128, 128},   // 1: 2 x 2 multiply waves of 64 x 64, 4 stages
-    {128, 256},   // 2: 2 x 2 multiply waves of 64 x 128, 4 stages, one K slice, two-term or fp16
+    {128, 256},   // 2: 2 x 2 multiply waves of 64 x 128, 4 stages, one K slice, two-term
 };
 
 template <int EPI>
@@ -724,14 +438,9 @@ void lds_epi(int c, const GemmArgs& a, bool partial, hipStream_t st) {
     case 0: lds_cfg<128, 192, 2, 2, 4, EPI>(a, partial, st); break;
     case 1: lds_cfg<128, 128, 2, 2, 4, EPI>(a, partial, st); break;
     default: {
-      // one K slice; two-term activations (the in-place refill needs both
-      // terms) or single-term fp16 ones (one fragment set of each kind)
+      // one K slice of two-term activations (the in-place refill needs both terms)
       const int grid = gemm_grid_size(a.N / 256, (a.M + 127) / 128, 1);
-      if (a.f16) {
-        if constexpr (EPI == EPI_SWIGLU) gemm_lds_kernel<128, 256, 2, 2, 4, EPI, false, 0, true><<<grid, 512, 0, st>>>(a);
-      } else {
-        gemm_lds_kernel<128, 256, 2, 2, 4, EPI, true, 0><<<grid, 512, 0, st>>>(a);
-      }
+      gemm_lds_kernel<128, 256, 2, 2, 4, EPI, true, 0><<<grid, 512, 0, st>>>(a);
       break;
     }
   }
@@ -750,7 +459,7 @@ bool gemm_lds_cfg_ok(int c, const GemmArgs& a) {
   if (c < 0 || c >= GEMM_NCFG_LDS) return false;
   const LdsCfg& k = kLds[c];
   if (a.M <= 0 || a.N % k.BN || a.ksplit < 1 || a.K % (a.ksplit * BK)) return false;
-  if (c == 2 && ((!a.A2 && !a.f16) || a.ksplit != 1)) return false;
+  if (c == 2 && (!a.A2 || a.ksplit != 1)) return false;
   // 32-bit lane offsets
   if ((size_t)a.N * (a.w_tiled ? BK : a.ldw) * 2 >= (1ull << 32) || (size_t)a.M * (a.a_tiled ? BK : a.lda) * 2 >= (1ull << 32))
     return false;

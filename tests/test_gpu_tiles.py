@@ -1,0 +1,47 @@
+"""The tiles a projection takes depend on the rows of its pass; the bits do not.
+
+In a context of one K slice (2048 or more response rows) every sequence's
+cached step is computed twice: in the whole batch's pass (wide tiles) and alone
+(128-row tiles, which the other GPU tests hold against the oracle).  Short
+prompts keep attention in one split in both, so the logits must be the same
+bits; the last row tile of the batch is ragged.
+"""
+
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import dev_i32, make_ctx, say, with_gains
+from synth.gen import model_weights
+from synth.workloads import ModelShape
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,hq,hkv,hd,F,fp16,B,G", [
+    (128, 32, 32, 128, 12288, True, 15, 264),    # QKV 256 x 256; fp16 gate/up 256 x 256; 3960 rows
+    (128, 32, 32, 128, 12288, False, 16, 256),   # two-term gate/up 256 x 256; whole tiles
+    (192, 36, 4, 64, 6336, True, 15, 264),       # fp16 gate/up 256 x 192; QKV tiles that straddle the value heads
+    (64, 32, 16, 64, 6336, False, 10, 416),      # two-term gate/up 256 x 192; two k steps; 4160 rows
+    (4096, 2, 2, 64, 128, True, 16, 256),        # O and down 256 x 256
+    (128, 28, 4, 128, 12288, True, 8, 256),      # Dream-like heads at 2048 rows: QKV 256 x 192
+])
+def test_batch_pass_equals_single_passes(d, hq, hkv, hd, F, fp16, B, G):
+    say(f"tiles d={d} heads={hq}/{hkv}x{hd} F={F} fp16={fp16} rows={B * G}")
+    m = ModelShape(n_layers=2, d_model=d, n_heads=hq, n_kv_heads=hkv, head_dim=hd, d_ff=F, vocab=512, dtype="bf16",
+                   gateup_fp16=fp16, init_std=0.05)
+    ctx = make_ctx(m, with_gains(model_weights(m, seed=3), 4), B, 8, 8 * B, G)
+    rng = np.random.default_rng(5)
+    prompt = dev_i32(rng.integers(0, m.mask_id, 8 * B))
+    g0 = rng.integers(0, m.mask_id, (B, G)).astype(np.int32)
+    z_full = ctx.refresh_prompt(prompt, [8] * B, dev_i32(g0))
+    g1 = dev_i32(np.where(rng.random((B, G)) < 0.3, m.mask_id, g0))
+    z = ctx.step(g1)
+    assert bool(torch.isfinite(z).all()) and bool(torch.isfinite(z_full).all())
+    for b in (0, B // 2, B - 1):
+        sel = [i == b for i in range(B)]
+        alone = ctx.step(g1, seq_sel=sel, logits=torch.full_like(z, 7.0))
+        assert bool((alone[b] == z[b]).all()), b
+        assert bool((alone[(b + 1) % B] == 7.0).all())
+        again = ctx.refresh_prompt(prompt, [8] * B, dev_i32(g0), seq_sel=sel, logits=torch.full_like(z, 7.0))
+        assert bool((again[b] == z_full[b]).all()), b
