@@ -276,7 +276,8 @@ SeqPlan build_plan(const archer_ctx* c, bool full, const std::vector<int>& sel) 
 void gemm_prepare(archer_ctx* c, GemmArgs& a) {
   if (!is_bf16(c)) return;
   a.ksplit = gemm_ksplit(a.N, a.K, c->L.Rmax);
-  if (a.M <= c->L.part_rows) a.part = c->at<float>(c->L.part);
+  a.part = c->at<float>(c->L.part);
+  a.part_rows = c->L.part_rows;
 }
 
 archer_status gemm(archer_ctx* c, int cls, int epi, GemmArgs& a) {

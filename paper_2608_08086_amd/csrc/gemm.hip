@@ -489,6 +489,11 @@ int gemm_ksplit(int N, int K, int rows) {
   return S;
 }
 
+// One workgroup per slice with a separate reduction: measured on the LLaDA-8B
+// projections at 256 .. 4352 rows, at least as fast as folding the slices into
+// one workgroup wherever the partial buffer holds the rows.
+static bool use_partials(const GemmArgs& a) { return a.ksplit > 1 && a.part && a.M <= a.part_rows; }
+
 // Time of one round of a one-slice launch's tiles (256 workgroups, one per CU)
 // in us at K 4096, measured on the LLaDA-8B projections with full rounds (the
 // ragged batch's 4096- and 24853-row passes; 768- and 4352-row passes order the
@@ -515,6 +520,24 @@ static bool one_slice_ok(int cfg, const GemmArgs& a, int epi) {
   return cfg >= GEMM_NCFG + GEMM_NCFG_LDS ? gemm_wide_ok(cfg, a, epi) : gemm_lds_cfg_ok(cfg - GEMM_NCFG, a);
 }
 
+// The one-slice configuration with the least rounds times round time, and that
+// time in us; -1 if there is none.
+static int one_slice_pick(const GemmArgs& a, int epi, double* cost) {
+  int best = -1;
+  for (int cfg : {(int)GEMM_WIDE_256x256, (int)GEMM_WIDE_256x192, GEMM_NCFG + 2, (int)GEMM_WIDE_128x192, GEMM_NCFG + 0,
+                  GEMM_NCFG + 1}) {
+    const double t = tile_round_us(cfg, a.f16 != 0) * a.K / 4096;
+    int bm, bn;
+    tile_size(cfg, &bm, &bn);
+    if (t == 0.0 || (epi == EPI_STORE && bn != 256) || !one_slice_ok(cfg, a, epi)) continue;
+    // the grid counts what the fullest XCD gets of the tile order, eight times over
+    const int grid = gemm_grid_size(a.N / bn, (a.M + bm - 1) / bm, 1);
+    const double c = (double)((grid + 255) / 256) * t;
+    if (best < 0 || c < 0.98 * *cost) { best = cfg; *cost = c; }
+  }
+  return best;
+}
+
 int gemm_pick_cfg(const GemmArgs& a, int epi) {
   // One K slice with two-term or fp16 operands: the tile with the least rounds of 256 workgroups
   // times the time of a round; of two within 2 % the wider one (so, for example,
@@ -529,22 +552,12 @@ int gemm_pick_cfg(const GemmArgs& a, int epi) {
   // waves per SIMD).
   const bool head = epi == EPI_STORE;
   if ((a.A2 || a.f16) && a.ksplit == 1 && (!head || (a.N % 256 == 0 && a.N / 256 >= 256))) {
-    int best = -1;
-    double bc = 0;
-    for (int cfg : {(int)GEMM_WIDE_256x256, (int)GEMM_WIDE_256x192, GEMM_NCFG + 2, (int)GEMM_WIDE_128x192, GEMM_NCFG + 0,
-                    GEMM_NCFG + 1}) {
-      const double t = tile_round_us(cfg, a.f16 != 0);
-      int bm, bn;
-      tile_size(cfg, &bm, &bn);
-      if (t == 0.0 || (head && bn != 256) || !one_slice_ok(cfg, a, epi)) continue;
-      const long wgs = (long)(a.N / bn) * ((a.M + bm - 1) / bm);
-      const double c = (double)((wgs + 255) / 256) * t;
-      if (best < 0 || c < 0.98 * bc) { best = cfg; bc = c; }
-    }
+    double cost;
+    const int best = one_slice_pick(a, epi, &cost);
     if (best >= 0) return best;
   }
   if (a.N % 192 == 0 && gemm_lds_cfg_ok(0, a)) {
-    const bool fold = a.ksplit > 1 && !(a.part && gemm_partial_wanted(GEMM_NCFG + 0, a));
+    const bool fold = a.ksplit > 1 && !use_partials(a);
     if (!fold) return GEMM_NCFG + 0;
   }
   if (a.N % 128 == 0 && gemm_lds_cfg_ok(1, a)) return GEMM_NCFG + 1;
@@ -567,14 +580,6 @@ bool gemm_cfg_ok(int cfg, const GemmArgs& a, int epi) {
   if (epi == EPI_QKV && (a.hd % BN)) return false;
   if (epi == EPI_SWIGLU && ((a.N / 2) % (BN / 2))) return false;
   return true;
-}
-
-int gemm_partial_wanted(int cfg, const GemmArgs& a) {
-  // Measured on MI355X (LLaDA-8B projections, M = 256 .. 4352): one workgroup
-  // per slice with a separate reduction is at least as fast as folding the
-  // slices into one workgroup whenever a partial buffer is available.
-  (void)cfg;
-  return a.ksplit > 1;
 }
 
 bool gemm_args_ok(int epi, const GemmArgs& a) {
@@ -608,16 +613,85 @@ int launch_gemm_bf16_cfg(int epi, int cfg, bool partial, const GemmArgs& a, hipS
   return 0;
 }
 
+// Rows [0, m1) of a launch that run as one-slice 256 x 256 tiles in whole rounds
+// of the 256 CUs, ahead of the rest with its own configuration; 0: one launch.
+//
+// A launch whose last round is nearly empty pays for a whole one: the 4352 rows
+// of a 4096-token refresh are 17 row tiles, 3.19 rounds of QKV tiles.  Rounds of
+// 16 row tiles and 256 rows apart took 553 + 53 us against 628, and O and down
+// (one round and 256 rows in split-K slices, 189 + 33 and 522 + 58 us) also drop
+// the partial planes of the large part: 275 + 89 and 724 + 93 us with every row
+// in 4 slices.  LAUNCH_US is the drain and start of the second launch.  Rows
+// of a split-K context then sum K in one slice or in several depending on
+// their place in a large pass (as attention splits its keys per pass); passes
+// short of a whole round, every cached pass of such a context, are not touched.
+static int gemm_split_rows(const GemmArgs& a, int epi) {
+  constexpr double LAUNCH_US = 8.0;
+  if (epi == EPI_STORE || !(a.A2 || a.f16) || a.N % 256) return 0;
+  GemmArgs one = a;
+  one.ksplit = 1;
+  if (!gemm_wide_ok(GEMM_WIDE_256x256, one, epi)) return 0;
+  const double t = tile_round_us(GEMM_WIDE_256x256, a.f16 != 0) * a.K / 4096;
+  // one launch of m rows in the context's slices
+  const auto plain = [&](int m) {
+    GemmArgs r = a;
+    r.M = m;
+    double c = 0.0;
+    if (a.ksplit == 1) return one_slice_pick(r, epi, &c) >= 0 ? c : 1e30;
+    const int grid = gemm_grid_size((a.N + 127) / 128, (m + 127) / 128, a.ksplit);
+    c = (double)((grid + 255) / 256) * tile_round_us(GEMM_NCFG + 1, a.f16 != 0) * a.K / 4096 / a.ksplit;
+    // the reduction reads the planes and the destination and writes it at about 4 TB/s
+    return c + LAUNCH_US + (double)m * a.N * 4 * (a.ksplit + 2) / 4e6;
+  };
+  const int nt = a.N / 256, mt_all = a.M / 256;
+  double best = 0.98 * plain(a.M);
+  int m1 = 0;
+  for (int r = 1; (long)r * 256 / nt <= mt_all; ++r) {
+    // as many row tiles as r rounds of CUs hold, in equal shares where XCDs split the row tiles
+    int mt = (int)((long)r * 256 / nt);
+    mt -= mt % tile_py(nt, mt);
+    if (mt == 0 || gemm_grid_size(nt, mt, 1) > r * 256) continue;
+    const double c = r * t + (mt * 256 < a.M ? LAUNCH_US + plain(a.M - mt * 256) : 0.0);
+    if (c < best) { best = c; m1 = mt * 256; }
+  }
+  return m1;
+}
+
 bool gemm_fuses_norm(const GemmArgs& a) {
-  if (!a.ngain || !a.part || a.N % 4 || a.N > 16 * NORM_THREADS || a.ldx % 4 || a.ksplit > 8) return false;
-  const int cfg = gemm_pick_cfg(a, EPI_RESID);
-  return gemm_partial_wanted(cfg, a) != 0;
+  if (!a.ngain || a.N % 4 || a.N > 16 * NORM_THREADS || a.ldx % 4 || a.ksplit > 8) return false;
+  return use_partials(a) && gemm_split_rows(a, EPI_RESID) == 0;
+}
+
+// The arguments of rows [r0, r0 + m) of a launch (r0 a multiple of 256).
+static GemmArgs gemm_rows(const GemmArgs& a, int r0, int m) {
+  GemmArgs b = a;
+  const auto act = [&](const void* p, int ld, int tiled) {
+    return p ? (const void*)((const char*)p + (size_t)r0 * (tiled ? 32 : ld) * 2) : nullptr;
+  };
+  b.M = m;
+  b.A = act(a.A, a.lda, a.a_tiled);
+  b.A2 = act(a.A2, a.lda, a.a_tiled);
+  b.H = (void*)act(a.H, a.ldh, a.h_tiled);
+  b.H2 = (void*)act(a.H2, a.ldh, a.h_tiled);
+  if (a.X) b.X = a.X + (size_t)r0 * a.ldx;
+  if (a.Qb) b.Qb = (char*)a.Qb + (size_t)r0 * a.hd * 2;
+  if (a.row_pos) b.row_pos = a.row_pos + r0;
+  if (a.row_dst) b.row_dst = a.row_dst + r0;
+  b.ngain = nullptr;   // the normalisation of the updated rows runs on all of them together
+  return b;
 }
 
 int launch_gemm_bf16(int epi, const GemmArgs& a, hipStream_t st) {
-  const int cfg = gemm_pick_cfg(a, epi);
-  const bool partial = a.part != nullptr && gemm_partial_wanted(cfg, a);
-  return launch_gemm_bf16_cfg(epi, cfg, partial, a, st);
+  if (!gemm_args_ok(epi, a)) return 1;
+  if (const int m1 = gemm_split_rows(a, epi)) {
+    GemmArgs b = gemm_rows(a, 0, m1);
+    b.ksplit = 1;
+    const int rc = launch_gemm_wide(epi, GEMM_WIDE_256x256, b, st);
+    if (rc || m1 == a.M) return rc;
+    const GemmArgs c = gemm_rows(a, m1, a.M - m1);
+    return launch_gemm_bf16_cfg(epi, gemm_pick_cfg(c, epi), use_partials(c), c, st);
+  }
+  return launch_gemm_bf16_cfg(epi, gemm_pick_cfg(a, epi), use_partials(a), a, st);
 }
 
 // ---------------------------------------------------------------------------

@@ -22,7 +22,8 @@ struct GemmArgs {
   int w_tiled;                           //   k-block-major W (ldw = rows of each matrix), see act_at
   int M, N, K;
   int ksplit;                            // K slices (bf16): fixed per (N, K, context), see gemm_ksplit
-  float* part;                           // fp32 partials [ksplit][M][N] for the per-slice launch, or null
+  float* part; int part_rows;            // fp32 partials [ksplit][M][N] for per-slice launches of up to part_rows
+                                         //   rows, or null
   float* C; int ldc; const int* out_row; // EPI_STORE (C may be null when tstat is set: statistics only)
   // EPI_STORE with decision statistics (LM head; see stat_col in common.h):
   // partials tstat / targ [logits row][2 N / BN], the current token's logit
@@ -127,7 +128,6 @@ int launch_gemm_lds_cfg(int epi, int c, bool partial, const GemmArgs& a, hipStre
 void launch_gemm_reduce(int epi, const GemmArgs& a, hipStream_t st);
 int gemm_grid_size(int n_tiles, int m_tiles, int S);
 int gemm_pick_cfg(const GemmArgs& a, int epi);
-int gemm_partial_wanted(int cfg, const GemmArgs& a);
 int launch_gemm_bf16_cfg(int epi, int cfg, bool partial, const GemmArgs& a, hipStream_t st);
 int launch_gemm_bf16(int epi, const GemmArgs& a, hipStream_t st);
 // Column tile of the LM-head GEMM when it can also produce the decision
