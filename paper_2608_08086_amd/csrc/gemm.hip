@@ -504,6 +504,8 @@ static double tile_round_us(int cfg, bool f16) {
     case GEMM_NCFG + 1: return f16 ? 37.0 : 53.0;      // 128 x 128
     case GEMM_NCFG + 0: return f16 ? 0.0 : 79.5;       // 128 x 192
     case GEMM_NCFG + 2: return f16 ? 0.0 : 93.5;       // 128 x 256
+    case GEMM_NCFG + 3: return f16 ? 0.0 : 50.0;       // 64 x 192 (256 and 768 rows)
+    case GEMM_NCFG + 4: return f16 ? 0.0 : 37.0;       // 64 x 128 (120 to 768 rows: 33 to 39)
     case GEMM_WIDE_128x192: return f16 ? 45.0 : 0.0;
     case GEMM_WIDE_256x192: return f16 ? 75.0 : 140.0;
     case GEMM_WIDE_256x256: return f16 ? 98.5 : 180.0;
@@ -512,12 +514,25 @@ static double tile_round_us(int cfg, bool f16) {
 }
 
 static void tile_size(int cfg, int* bm, int* bn) {
-  *bm = cfg == GEMM_WIDE_256x256 || cfg == GEMM_WIDE_256x192 ? 256 : 128;
-  *bn = cfg == GEMM_WIDE_256x256 || cfg == GEMM_NCFG + 2 ? 256 : cfg == GEMM_NCFG + 1 ? 128 : 192;
+  const bool rows64 = cfg == GEMM_NCFG + 3 || cfg == GEMM_NCFG + 4;
+  *bm = cfg == GEMM_WIDE_256x256 || cfg == GEMM_WIDE_256x192 ? 256 : rows64 ? 64 : 128;
+  *bn = cfg == GEMM_WIDE_256x256 || cfg == GEMM_NCFG + 2 ? 256
+        : cfg == GEMM_NCFG + 1 || cfg == GEMM_NCFG + 4   ? 128
+                                                         : 192;
 }
 
 static bool one_slice_ok(int cfg, const GemmArgs& a, int epi) {
   return cfg >= GEMM_NCFG + GEMM_NCFG_LDS ? gemm_wide_ok(cfg, a, epi) : gemm_lds_cfg_ok(cfg - GEMM_NCFG, a);
+}
+
+// Rounds of 256 workgroups of a launch in S slices times the time of a round, in
+// us; 0: not a configuration of the kind.  The grid counts what the fullest XCD
+// gets of the tile order, eight times over.
+static double rounds_us(int cfg, const GemmArgs& a, int S) {
+  int bm, bn;
+  tile_size(cfg, &bm, &bn);
+  const int grid = gemm_grid_size(a.N / bn, (a.M + bm - 1) / bm, S);
+  return (double)((grid + 255) / 256) * tile_round_us(cfg, a.f16 != 0) * a.K / 4096 / S;
 }
 
 // The one-slice configuration with the least rounds times round time, and that
@@ -525,14 +540,22 @@ static bool one_slice_ok(int cfg, const GemmArgs& a, int epi) {
 static int one_slice_pick(const GemmArgs& a, int epi, double* cost) {
   int best = -1;
   for (int cfg : {(int)GEMM_WIDE_256x256, (int)GEMM_WIDE_256x192, GEMM_NCFG + 2, (int)GEMM_WIDE_128x192, GEMM_NCFG + 0,
-                  GEMM_NCFG + 1}) {
-    const double t = tile_round_us(cfg, a.f16 != 0) * a.K / 4096;
+                  GEMM_NCFG + 1, GEMM_NCFG + 3, GEMM_NCFG + 4}) {
     int bm, bn;
     tile_size(cfg, &bm, &bn);
-    if (t == 0.0 || (epi == EPI_STORE && bn != 256) || !one_slice_ok(cfg, a, epi)) continue;
-    // the grid counts what the fullest XCD gets of the tile order, eight times over
-    const int grid = gemm_grid_size(a.N / bn, (a.M + bm - 1) / bm, 1);
-    const double c = (double)((grid + 255) / 256) * t;
+    if ((epi == EPI_STORE && bn != 256) || !one_slice_ok(cfg, a, epi)) continue;
+    const double c = rounds_us(cfg, a, 1);
+    if (c != 0.0 && (best < 0 || c < 0.98 * *cost)) { best = cfg; *cost = c; }
+  }
+  return best;
+}
+
+// The same for a two-term launch whose slices are workgroups of their own; -1 if there is none.
+static int split_pick(const GemmArgs& a, double* cost) {
+  int best = -1;
+  for (int cfg : {GEMM_NCFG + 0, GEMM_NCFG + 1, GEMM_NCFG + 3, GEMM_NCFG + 4}) {
+    if (!gemm_lds_cfg_ok(cfg - GEMM_NCFG, a)) continue;
+    const double c = rounds_us(cfg, a, a.ksplit);
     if (best < 0 || c < 0.98 * *cost) { best = cfg; *cost = c; }
   }
   return best;
@@ -546,14 +569,21 @@ int gemm_pick_cfg(const GemmArgs& a, int epi) {
   // throughout).  The LM head takes the column tile by N alone (256, when N has
   // at least 256 of them), so that the partials of its fused decision statistics
   // do not depend on the row count of a pass.
-  // Split-K launches take 128 x 192 tiles when N is a multiple of 192, else
-  // 128 x 128; the 128 x 192 tile is not used for slices folded in one
-  // workgroup (its second accumulator set does not fit the registers of two
-  // waves per SIMD).
+  // Two-term split-K launches choose the same way among the 128- and 64-row tiles
+  // of up to 192 columns (down at 120 rows in 4 slices: 64 x 128 tiles 35 us,
+  // 128 x 128 45; at 256 rows 63 and 51).  Other split-K launches take 128 x 192
+  // tiles when N is a multiple of 192, else 128 x 128; the 128 x 192 tile is not used
+  // for slices folded in one workgroup (its second accumulator set does not
+  // fit the registers of two waves per SIMD).
   const bool head = epi == EPI_STORE;
   if ((a.A2 || a.f16) && a.ksplit == 1 && (!head || (a.N % 256 == 0 && a.N / 256 >= 256))) {
     double cost;
     const int best = one_slice_pick(a, epi, &cost);
+    if (best >= 0) return best;
+  }
+  if (a.A2 && use_partials(a)) {
+    double cost;
+    const int best = split_pick(a, &cost);
     if (best >= 0) return best;
   }
   if (a.N % 192 == 0 && gemm_lds_cfg_ok(0, a)) {
@@ -638,8 +668,7 @@ static int gemm_split_rows(const GemmArgs& a, int epi) {
     r.M = m;
     double c = 0.0;
     if (a.ksplit == 1) return one_slice_pick(r, epi, &c) >= 0 ? c : 1e30;
-    const int grid = gemm_grid_size((a.N + 127) / 128, (m + 127) / 128, a.ksplit);
-    c = (double)((grid + 255) / 256) * tile_round_us(GEMM_NCFG + 1, a.f16 != 0) * a.K / 4096 / a.ksplit;
+    if (!a.A2 || split_pick(r, &c) < 0) c = rounds_us(GEMM_NCFG + 1, r, a.ksplit);
     // the reduction reads the planes and the destination and writes it at about 4 TB/s
     return c + LAUNCH_US + (double)m * a.N * 4 * (a.ksplit + 2) / 4e6;
   };

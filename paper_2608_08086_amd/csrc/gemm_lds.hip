@@ -430,13 +430,37 @@ const LdsCfg kLds[GEMM_NCFG_LDS] = {
     {128, 192},   // 0: 2 x 2 multiply waves of 64 x 96, 4 stages
     {128, 128},   // 1: 2 x 2 multiply waves of 64 x 64, 4 stages
     {128, 256},   // 2: 2 x 2 multiply waves of 64 x 128, 4 stages, one K slice, two-term
+    {64, 192},    // 3: 2 x 2 multiply waves of 32 x 96, 4 stages, two-term
+    {64, 128},    // 4: 2 x 2 multiply waves of 32 x 64, 4 stages, two-term
 };
+
+// 64-row tiles, for launches of few rows.  A workgroup of the small tiles gets
+// about 60 bytes per ns into its LDS, however many CUs run and however many
+// stages are in flight (4 and 7 alike), so a k step of a two-term launch costs
+// (2 BM + BN) x 64 bytes: beside two activation terms a row costs twice a
+// column, and 64 x 192 loads 20 KB where 128 x 128 loads 24 KB for 4 / 3 of the
+// products.  LLaDA-8B QKV at 256 rows (256 workgroups against 192) 55 -> 50 us,
+// at 120 rows 64 x 128 tiles 52 -> 39 us; down in 4 slices at 120 rows 45 -> 35 us.
+// fp16 launches have one activation term and gain nothing (81 us against 56 in
+// 128 x 192 tiles at 256 rows, 46 against 43 at 120).  Slices of separate workgroups only.
+template <int BN, int EPI>
+void lds_rows64(const GemmArgs& a, bool partial, hipStream_t st) {
+  const int grid = gemm_grid_size(a.N / BN, (a.M + 63) / 64, partial ? a.ksplit : 1);
+  if (partial) {
+    gemm_lds_kernel<64, BN, 2, 2, 4, EPI, true, 2><<<grid, 512, 0, st>>>(a);
+    launch_gemm_reduce(EPI, a, st);
+  } else if constexpr (EPI != EPI_STORE) {
+    gemm_lds_kernel<64, BN, 2, 2, 4, EPI, true, 0><<<grid, 512, 0, st>>>(a);
+  }
+}
 
 template <int EPI>
 void lds_epi(int c, const GemmArgs& a, bool partial, hipStream_t st) {
   switch (c) {
     case 0: lds_cfg<128, 192, 2, 2, 4, EPI>(a, partial, st); break;
     case 1: lds_cfg<128, 128, 2, 2, 4, EPI>(a, partial, st); break;
+    case 3: lds_rows64<192, EPI>(a, partial, st); break;
+    case 4: lds_rows64<128, EPI>(a, partial, st); break;
     default: {
       // one K slice of two-term activations (the in-place refill needs both terms)
       const int grid = gemm_grid_size(a.N / 256, (a.M + 127) / 128, 1);
@@ -460,6 +484,7 @@ bool gemm_lds_cfg_ok(int c, const GemmArgs& a) {
   const LdsCfg& k = kLds[c];
   if (a.M <= 0 || a.N % k.BN || a.ksplit < 1 || a.K % (a.ksplit * BK)) return false;
   if (c == 2 && (!a.A2 || a.ksplit != 1)) return false;
+  if (c >= 3 && !a.A2) return false;
   // 32-bit lane offsets
   if ((size_t)a.N * (a.w_tiled ? BK : a.ldw) * 2 >= (1ull << 32) || (size_t)a.M * (a.a_tiled ? BK : a.lda) * 2 >= (1ull << 32))
     return false;
@@ -474,6 +499,7 @@ int gemm_lds_tiles(int c, const GemmArgs& a) {
 int launch_gemm_lds_cfg(int epi, int c, bool partial, const GemmArgs& a, hipStream_t st) {
   if (!gemm_args_ok(epi, a) || !gemm_lds_cfg_ok(c, a)) return 1;
   if (partial && (!a.part || a.ksplit < 2)) return 1;
+  if (c >= 3 && !partial && (a.ksplit != 1 || epi == EPI_STORE)) return 1;
   switch (epi) {
     case EPI_STORE: lds_epi<EPI_STORE>(c, a, partial, st); break;
     case EPI_RESID: lds_epi<EPI_RESID>(c, a, partial, st); break;

@@ -117,7 +117,7 @@ void launch_read_act(const void* hi, const void* lo, int n, int d, int ld, int t
 // (gemm_lds.hip); the GEMM_WIDE_ ones after them: wide tiles of one K slice
 // (gemm_wide.hip).  All give the same bits for the same (N, K) split.
 constexpr int GEMM_NCFG = 7;
-constexpr int GEMM_NCFG_LDS = 3;
+constexpr int GEMM_NCFG_LDS = 5;
 enum { GEMM_WIDE_256x256 = GEMM_NCFG + GEMM_NCFG_LDS, GEMM_WIDE_256x192, GEMM_WIDE_128x192 };
 bool gemm_wide_ok(int c, const GemmArgs& a, int epi);
 int launch_gemm_wide(int epi, int c, const GemmArgs& a, hipStream_t st);

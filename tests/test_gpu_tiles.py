@@ -71,3 +71,48 @@ def test_large_pass_of_split_k_context_matches_oracle(P, G):
     say(f"  max abs err full {err:.2e} cached {errc:.2e}")
     # logits of order 1; two-term operands and fp16 q, k, v (the two-layer full-width models stay below 4e-3)
     assert err < 8e-3 and errc < 8e-3
+
+
+@pytest.mark.parametrize("G,B", [(64, 32), (72, 29), (120, 18), (256, 8)])
+def test_few_row_pass_equals_batch_pass(G, B):
+    """64-row tiles (one sequence alone: 64 x 128, at 256 rows 64 x 192 for QKV) give the bits of the batch's wide
+    tiles; 72 and 120 rows leave a ragged last tile."""
+    say(f"few rows G={G} B={B}")
+    m = ModelShape(n_layers=2, d_model=128, n_heads=32, n_kv_heads=32, head_dim=128, d_ff=12288, vocab=512,
+                   dtype="bf16", gateup_fp16=False, init_std=0.05)
+    ctx = make_ctx(m, with_gains(model_weights(m, seed=3), 4), B, 8, 8 * B, G)
+    rng = np.random.default_rng(G)
+    g0 = rng.integers(0, m.mask_id, (B, G)).astype(np.int32)
+    ctx.refresh_prompt(dev_i32(rng.integers(0, m.mask_id, 8 * B)), [8] * B, dev_i32(g0))
+    g1 = dev_i32(np.where(rng.random((B, G)) < 0.3, m.mask_id, g0))
+    z = ctx.step(g1)
+    assert bool(torch.isfinite(z).all())
+    for b in (0, B - 1):
+        alone = ctx.step(g1, seq_sel=[i == b for i in range(B)], logits=torch.full_like(z, 7.0))
+        assert bool((alone[b] == z[b]).all()), b
+
+
+@pytest.mark.parametrize("d,hq,hkv,hd,F,P,G", [
+    (4096, 2, 2, 64, 512, 5, 64),      # O and down in slices of 64 x 128 tiles, one row tile
+    (4096, 2, 2, 64, 512, 9, 72),      # a ragged second row tile
+    (4096, 2, 2, 64, 512, 60, 128),    # two row tiles; the refresh in 128-row ones
+    (3584, 28, 4, 128, 128, 7, 128),   # QKV in slices of 64 x 192 tiles
+])
+def test_few_row_split_k_pass_matches_oracle(d, hq, hkv, hd, F, P, G):
+    say(f"few rows split K d={d} G={G}")
+    m = ModelShape(n_layers=2, d_model=d, n_heads=hq, n_kv_heads=hkv, head_dim=hd, d_ff=F, vocab=256, dtype="bf16",
+                   init_std=0.02)
+    W = with_gains(model_weights(m, seed=8), 9)
+    ctx = make_ctx(m, W, 1, P, P, G)
+    rng = np.random.default_rng(P)
+    p = rng.integers(0, m.mask_id, P)
+    g0 = np.full(G, m.mask_id)
+    z = host(ctx.refresh_prompt(dev_i32(p), [P], dev_i32(g0[None])))[0]
+    z_ref, cache, _ = om.full_forward(W, m, p, g0)
+    g1 = np.where(rng.random(G) < 0.5, rng.integers(0, m.mask_id, G), g0)
+    zc = host(ctx.step(dev_i32(g1[None])))[0]
+    zc_ref, _ = om.cached_forward(W, m, g1, cache, P)
+    err, errc = np.max(np.abs(z - z_ref)), np.max(np.abs(zc - zc_ref))
+    say(f"  max abs err full {err:.2e} cached {errc:.2e}")
+    # the bound of the larger passes above, with the same operands
+    assert err < 8e-3 and errc < 8e-3
