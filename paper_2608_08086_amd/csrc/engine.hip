@@ -341,31 +341,31 @@ archer_status run_forward(archer_ctx* c, bool full, const std::vector<int>& sel,
   int* row_dst = c->at<int>(L.row_dst);
   archer_status st;
 
-  st = timed(c, ARCHER_K_EMBED, (double)rows * d * (es + 4), 0.0, [&] {
+  // bf16 activations that feed a projection GEMM are stored k-block-major
+  // with the buffer's row capacity as ld (act, O, H: Mmax rows; Cn: Rmax)
+  const int tiled = is_bf16(c) ? 1 : 0;
+  // the embedding rows and, from them, the first layer's attn_norm
+  st = timed(c, ARCHER_K_EMBED, (double)rows * d * (es * (act2_qkv ? 3 : 2) + 4), 0.0, [&] {
+    int* out_row = c->at<int>(L.out_row);
+    int* err = c->at<int>(L.err);
     if (is_bf16(c))
-      launch_embed<bf16>(pl, c->tok_emb, d, m.vocab, m.mask_id, prompt, resp, x, row_pos, row_dst,
-                         c->at<int>(L.g_anchor), c->at<int>(L.err), c->stream);
+      launch_embed<bf16>(pl, c->tok_emb, d, m.vocab, m.mask_id, prompt, resp, x, row_pos, row_dst, out_row,
+                         c->at<int>(L.g_anchor), err, c->attn_norm[0], act, act2_qkv, L.Mmax, tiled, m.rms_eps, c->stream);
     else
-      launch_embed<float>(pl, c->tok_emb, d, m.vocab, m.mask_id, prompt, resp, x, row_pos, row_dst,
-                          c->at<int>(L.g_anchor), c->at<int>(L.err), c->stream);
+      launch_embed<float>(pl, c->tok_emb, d, m.vocab, m.mask_id, prompt, resp, x, row_pos, row_dst, out_row,
+                          c->at<int>(L.g_anchor), err, c->attn_norm[0], act, nullptr, d, tiled, m.rms_eps, c->stream);
     return 0;
   });
   if (st) return st;
 
-  // bf16 activations that feed a projection GEMM are stored k-block-major
-  // with the buffer's row capacity as ld (act, O, H: Mmax rows; Cn: Rmax)
-  const int tiled = is_bf16(c) ? 1 : 0;
-  auto norm = [&](const float* gain, int gather, int nrows, void* out, void* out2, int cap, bool half = false) {
+  auto norm = [&](const float* gain, int nrows, void* out, void* out2, int cap, bool half = false) {
     return timed(c, ARCHER_K_NORM, (double)nrows * d * (4 + es * (out2 ? 2 : 1)), 0.0, [&] {
       if (half)
-        launch_rmsnorm<f16>(*P, gather, nrows, x, gain, out, nullptr, cap, 1, d, m.rms_eps, c->at<int>(L.out_row),
-                            c->stream);
+        launch_rmsnorm<f16>(nrows, x, gain, out, nullptr, cap, 1, d, m.rms_eps, c->stream);
       else if (is_bf16(c))
-        launch_rmsnorm<bf16>(*P, gather, nrows, x, gain, out, out2, cap, 1, d, m.rms_eps, c->at<int>(L.out_row),
-                             c->stream);
+        launch_rmsnorm<bf16>(nrows, x, gain, out, out2, cap, 1, d, m.rms_eps, c->stream);
       else
-        launch_rmsnorm<float>(*P, gather, nrows, x, gain, out, out2, d, 0, d, m.rms_eps, c->at<int>(L.out_row),
-                              c->stream);
+        launch_rmsnorm<float>(nrows, x, gain, out, out2, d, 0, d, m.rms_eps, c->stream);
       return 0;
     });
   };
@@ -380,14 +380,14 @@ archer_status run_forward(archer_ctx* c, bool full, const std::vector<int>& sel,
 
   // RMSNorms whose input is the residual just updated by a split-K GEMM run
   // inside that GEMM's reduction (same arithmetic as the stand-alone kernel)
-  auto fuse_norm = [&](GemmArgs& a, const float* gain, void* out2, bool half = false) {
+  auto fuse_norm = [&](GemmArgs& a, const float* gain, void* out, void* out2, int ld, bool half = false) {
     if (!is_bf16(c)) return;
-    a.ngain = gain; a.nout = act; a.nout2 = out2; a.neps = m.rms_eps; a.nld = L.Mmax; a.ntiled = 1;
+    a.ngain = gain; a.nout = out; a.nout2 = out2; a.neps = m.rms_eps; a.nld = ld; a.ntiled = 1;
     a.nf16 = half ? 1 : 0;
   };
-  bool normed = false;   // attn_norm of the current layer already applied
+  bool normed = true;   // the next RMSNorm is already applied (the first layer's with the embedding)
   for (int l = 0; l < m.n_layers; ++l) {
-    if (!normed && (st = norm(c->attn_norm[l], 0, rows, act, act2_qkv, L.Mmax))) return st;
+    if (!normed && (st = norm(c->attn_norm[l], rows, act, act2_qkv, L.Mmax))) return st;
     normed = false;
     {
       GemmArgs a = gargs(act, tiled ? L.Mmax : d, c->w_qkv[l], c->w_tiled ? qkv_n : d, rows, qkv_n, d);
@@ -404,7 +404,8 @@ archer_status run_forward(archer_ctx* c, bool full, const std::vector<int>& sel,
     if (full && l + 1 == m.n_layers) {
       float* xc = c->at<float>(L.xc);
       void* qc = c->at<char>(L.Qc);
-      launch_gather_resp_rows(pl, x, xc, d, qbuf, qc, L.ldq, L.Rmax, hq, hd * (int)es, c->stream);
+      launch_gather_resp_rows(pl, x, xc, d, qbuf, qc, L.ldq, L.Rmax, hq, hd * (int)es,
+                              c->at<int>(L.out_row), c->stream);
       HIPCHK(hipGetLastError());
       P = &plc; rows = plc.rows; x = xc; qbuf = qc; ldq = L.Rmax;
     }
@@ -436,11 +437,11 @@ archer_status run_forward(archer_ctx* c, bool full, const std::vector<int>& sel,
                          d, hq * hd);
       a.A2 = o2; a.a_tiled = tiled; a.w_tiled = c->w_tiled;
       a.X = x; a.ldx = d;
-      fuse_norm(a, c->mlp_norm[l], act2_mlp, mlp16);
+      fuse_norm(a, c->mlp_norm[l], act, act2_mlp, L.Mmax, mlp16);
       if ((st = gemm(c, full ? ARCHER_K_GEMM_O_FULL : ARCHER_K_GEMM_O, EPI_RESID, a))) return st;
       normed = gemm_fuses_norm(a);
     }
-    if (!normed && (st = norm(c->mlp_norm[l], 0, rows, act, act2_mlp, L.Mmax, mlp16))) return st;
+    if (!normed && (st = norm(c->mlp_norm[l], rows, act, act2_mlp, L.Mmax, mlp16))) return st;
     normed = false;
     {
       GemmArgs a = gargs(act, tiled ? L.Mmax : d, c->w_gate[l], c->w_tiled ? F : d, rows, 2 * F, d);
@@ -453,13 +454,15 @@ archer_status run_forward(archer_ctx* c, bool full, const std::vector<int>& sel,
       GemmArgs a = gargs(c->at<char>(L.H), tiled ? L.Mmax : F, c->w_down[l], c->w_tiled ? d : F, rows, d, F);
       a.A2 = h2; a.a_tiled = tiled; a.w_tiled = c->w_tiled;
       a.X = x; a.ldx = d;
-      if (l + 1 < m.n_layers) fuse_norm(a, c->attn_norm[l + 1], act2_qkv);
+      // the rows after the last layer are the response rows in the LM head's order
+      if (l + 1 < m.n_layers) fuse_norm(a, c->attn_norm[l + 1], act, act2_qkv, L.Mmax);
+      else fuse_norm(a, c->final_norm, c->at<char>(L.Cn), cn2, L.Rmax);
       if ((st = gemm(c, full ? ARCHER_K_GEMM_DOWN_FULL : ARCHER_K_GEMM_DOWN, EPI_RESID, a))) return st;
       normed = gemm_fuses_norm(a);
     }
   }
   const int nresp = pl.n * pl.G;
-  if ((st = norm(c->final_norm, 1, nresp, c->at<char>(L.Cn), cn2, L.Rmax))) return st;
+  if (!normed && (st = norm(c->final_norm, nresp, c->at<char>(L.Cn), cn2, L.Rmax))) return st;
   {
     GemmArgs a = gargs(c->at<char>(L.Cn), tiled ? L.Rmax : d, c->lm_head, c->w_tiled ? m.vocab : d, nresp,
                        m.vocab, d);

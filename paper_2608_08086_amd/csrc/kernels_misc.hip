@@ -39,15 +39,28 @@ void launch_pack_kblock(const void* src, void* dst, int rows, int cols, hipStrea
 }
 
 // ---------------------------------------------------------------------------
-// Embedding gather.  One block per pass row: resolve (sequence, token,
-// position, K/V destination) from the plan, copy E[token] into the fp32
-// residual stream, and in a full pass record the response token as anchor g_r.
-template <class T>
-__global__ __launch_bounds__(256) void embed_kernel(SeqPlan pl, const T* __restrict__ emb, int d,
-                                                    int V, int mask_id, const int* __restrict__ prompt,
-                                                    const int* __restrict__ resp, float* __restrict__ x,
-                                                    int* __restrict__ row_pos, int* __restrict__ row_dst,
-                                                    int* __restrict__ g_anchor, int* __restrict__ err) {
+// Embedding gather with the first layer's RMSNorm.  One block per pass row:
+// resolve (sequence, token, position, K/V destination) from the plan, copy
+// E[token] into the fp32 residual stream, normalise it (the expressions of
+// rms_normalize_row, so the bits of a stand-alone RMSNorm) into the input of
+// the first QKV projection, and in a full pass record the response token as
+// anchor g_r, in a cached pass (response rows only) the logits row.
+// Few rows are bound by the chain plan -> token -> row -> sum, so a row's elements go
+// four to a load where the table is aligned for it (VEC), and the norm's second
+// look at them hits the cache.  With the final norm run in the last reduction, the
+// two-layer LLaDA-8B cached step at prompt 512 went from 467 to 453 us; 24853
+// rows save one read of the residual.
+template <class T, bool VEC>
+__global__ __launch_bounds__(NORM_THREADS) void embed_kernel(SeqPlan pl, const T* __restrict__ emb, int d, int V,
+                                                             int mask_id, const int* __restrict__ prompt,
+                                                             const int* __restrict__ resp, float* __restrict__ x,
+                                                             int* __restrict__ row_pos, int* __restrict__ row_dst,
+                                                             int* __restrict__ out_row, int* __restrict__ g_anchor,
+                                                             int* __restrict__ err, const float* __restrict__ gain,
+                                                             T* __restrict__ out, T* __restrict__ out2, int ld,
+                                                             int tiled, float eps) {
+  struct alignas(4 * sizeof(T)) quad { T e[4]; };
+  __shared__ float red[16];
   const int i = blockIdx.x;
   const int s = plan_find(pl.row_off, pl.n, i);
   const int j = i - pl.row_off[s];
@@ -63,7 +76,10 @@ __global__ __launch_bounds__(256) void embed_kernel(SeqPlan pl, const T* __restr
     tok = resp[b * G + r];
     pos = P + r;
     dst = b * G + r;
-    if (pl.full && threadIdx.x == 0) g_anchor[b * G + r] = tok;
+    if (threadIdx.x == 0) {
+      if (pl.full) g_anchor[b * G + r] = tok;
+      else out_row[i] = dst;
+    }
   }
   const bool bad = tok < 0 || tok >= V || (is_prompt && tok == mask_id);
   if (bad) {
@@ -76,52 +92,68 @@ __global__ __launch_bounds__(256) void embed_kernel(SeqPlan pl, const T* __restr
   }
   const T* e = emb + (size_t)tok * d;
   float* xr = x + (size_t)i * d;
-  for (int c = threadIdx.x; c < d; c += blockDim.x) xr[c] = to_f32(e[c]);
+  auto load4 = [&](int c) {
+    quad v;
+    if constexpr (VEC) {
+      v = *(const quad*)(e + c);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v.e[k] = e[c + k];
+    }
+    return make_float4(to_f32(v.e[0]), to_f32(v.e[1]), to_f32(v.e[2]), to_f32(v.e[3]));
+  };
+  float ss = 0.f;
+#pragma unroll 2
+  for (int c = threadIdx.x * 4; c < d; c += blockDim.x * 4) {
+    const float4 v = load4(c);
+    *(float4*)(xr + c) = v;
+    ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+  }
+  ss = block_sum(ss, red);
+  const float inv = 1.0f / sqrtf(ss / (float)d + eps);
+  for (int c = threadIdx.x * 4; c < d; c += blockDim.x * 4) {
+    const float4 v = load4(c);
+    const float4 g = *(const float4*)(gain + c);
+    store_act4<T>(out, out2, act_at(i, c, ld, tiled), v.x * inv * g.x, v.y * inv * g.y, v.z * inv * g.z, v.w * inv * g.w);
+  }
 }
 
 template <class T>
 void launch_embed(const SeqPlan& pl, const void* emb, int d, int V, int mask_id, const int* prompt,
-                  const int* resp, float* x, int* row_pos, int* row_dst, int* g_anchor, int* err,
-                  hipStream_t st) {
-  embed_kernel<T><<<pl.rows, 256, 0, st>>>(pl, (const T*)emb, d, V, mask_id, prompt, resp, x, row_pos,
-                                           row_dst, g_anchor, err);
+                  const int* resp, float* x, int* row_pos, int* row_dst, int* out_row, int* g_anchor, int* err,
+                  const float* gain, void* out, void* out2, int ld, int tiled, float eps, hipStream_t st) {
+  // d is a multiple of 64 and x a workspace row; the table is the caller's
+  auto run = [&](auto kernel) {
+    kernel<<<pl.rows, NORM_THREADS, 0, st>>>(pl, (const T*)emb, d, V, mask_id, prompt, resp, x, row_pos, row_dst, out_row,
+                                             g_anchor, err, gain, (T*)out, (T*)out2, ld, tiled, eps);
+  };
+  if (((uintptr_t)emb & (4 * sizeof(T) - 1)) == 0) run(embed_kernel<T, true>);
+  else run(embed_kernel<T, false>);
 }
-template void launch_embed<float>(const SeqPlan&, const void*, int, int, int, const int*, const int*,
-                                  float*, int*, int*, int*, int*, hipStream_t);
-template void launch_embed<bf16>(const SeqPlan&, const void*, int, int, int, const int*, const int*,
-                                 float*, int*, int*, int*, int*, hipStream_t);
+template void launch_embed<float>(const SeqPlan&, const void*, int, int, int, const int*, const int*, float*, int*,
+                                  int*, int*, int*, int*, const float*, void*, void*, int, int, float, hipStream_t);
+template void launch_embed<bf16>(const SeqPlan&, const void*, int, int, int, const int*, const int*, float*, int*,
+                                 int*, int*, int*, int*, const float*, void*, void*, int, int, float, hipStream_t);
 
 // ---------------------------------------------------------------------------
 // RMSNorm: out[r] = round_T(x[r] / sqrt(mean(x[r]^2) + eps) * gain), fp32 math.
-// gather = 1 (final norm): output row ri in [0, n*G) is response row ri % G of
-// pass sequence ri / G; its logits row b*G + (ri % G) is written to out_row.
 template <class T>
-__global__ __launch_bounds__(NORM_THREADS) void rmsnorm_kernel(SeqPlan pl, int gather, const float* __restrict__ x,
+__global__ __launch_bounds__(NORM_THREADS) void rmsnorm_kernel(const float* __restrict__ x,
                                                       const float* __restrict__ gain, T* __restrict__ out,
-                                                      T* __restrict__ out2, int ld, int tiled, int d, float eps,
-                                                      int* __restrict__ out_row) {
+                                                      T* __restrict__ out2, int ld, int tiled, int d, float eps) {
   __shared__ float red[16];
-  const int ro = blockIdx.x;
-  int ri = ro;
-  if (gather) {
-    const int s = ro / pl.G, r = ro % pl.G;
-    ri = pl.row_off[s] + (pl.full ? pl.p_len[s] : 0) + r;
-    if (threadIdx.x == 0) out_row[ro] = pl.seq[s] * pl.G + r;
-  }
-  rms_normalize_row<T>(x + (size_t)ri * d, gain, out, out2, ro, ld, tiled, d, eps, red);
+  const int row = blockIdx.x;
+  rms_normalize_row<T>(x + (size_t)row * d, gain, out, out2, row, ld, tiled, d, eps, red);
 }
 
 template <class T>
-void launch_rmsnorm(const SeqPlan& pl, int gather, int nrows, const float* x, const float* gain, void* out,
-                    void* out2, int ld, int tiled, int d, float eps, int* out_row, hipStream_t st) {
-  rmsnorm_kernel<T><<<nrows, NORM_THREADS, 0, st>>>(pl, gather, x, gain, (T*)out, (T*)out2, ld, tiled, d, eps, out_row);
+void launch_rmsnorm(int nrows, const float* x, const float* gain, void* out, void* out2, int ld, int tiled, int d,
+                    float eps, hipStream_t st) {
+  rmsnorm_kernel<T><<<nrows, NORM_THREADS, 0, st>>>(x, gain, (T*)out, (T*)out2, ld, tiled, d, eps);
 }
-template void launch_rmsnorm<float>(const SeqPlan&, int, int, const float*, const float*, void*, void*, int, int,
-                                    int, float, int*, hipStream_t);
-template void launch_rmsnorm<bf16>(const SeqPlan&, int, int, const float*, const float*, void*, void*, int, int,
-                                   int, float, int*, hipStream_t);
-template void launch_rmsnorm<f16>(const SeqPlan&, int, int, const float*, const float*, void*, void*, int, int,
-                                  int, float, int*, hipStream_t);
+template void launch_rmsnorm<float>(int, const float*, const float*, void*, void*, int, int, int, float, hipStream_t);
+template void launch_rmsnorm<bf16>(int, const float*, const float*, void*, void*, int, int, int, float, hipStream_t);
+template void launch_rmsnorm<f16>(int, const float*, const float*, void*, void*, int, int, int, float, hipStream_t);
 
 // ---------------------------------------------------------------------------
 // Decision pass 1: per response row, over the non-MASK vocabulary:
@@ -429,14 +461,16 @@ void launch_fill_i32(int* p, int v, size_t n, hipStream_t st) {
 // Response rows of a FullForward pass moved into the row layout of a
 // CachedForward pass (row s G + i of selected sequence s): the residual row
 // (d floats) and the query row of every head (Q [hq][ldq][hd], qbytes bytes
-// per row).  The last layer of a full pass needs nothing else of its prompt
+// per row), and the logits row of each.  The last layer of a full pass needs nothing else of its prompt
 // rows once their keys and values are in the cache, so it continues on the
 // response rows only.
 __global__ __launch_bounds__(256) void gather_resp_rows_kernel(SeqPlan pl, const float* __restrict__ x,
                                                                float* __restrict__ xc, int d,
                                                                const char* __restrict__ Q, char* __restrict__ Qc,
-                                                               int ldq, int ldqc, int hq, int qbytes) {
+                                                               int ldq, int ldqc, int hq, int qbytes,
+                                                               int* __restrict__ out_row) {
   const int r = blockIdx.x, s = r / pl.G, i = r % pl.G;
+  if (threadIdx.x == 0) out_row[r] = pl.seq[s] * pl.G + i;
   const int src = pl.row_off[s] + pl.p_len[s] + i;
   const float4* xs = (const float4*)(x + (size_t)src * d);
   float4* xd = (float4*)(xc + (size_t)r * d);
@@ -449,10 +483,10 @@ __global__ __launch_bounds__(256) void gather_resp_rows_kernel(SeqPlan pl, const
 }
 
 void launch_gather_resp_rows(const SeqPlan& pl, const float* x, float* xc, int d, const void* Q, void* Qc, int ldq,
-                             int ldqc, int hq, int qbytes, hipStream_t st) {
+                             int ldqc, int hq, int qbytes, int* out_row, hipStream_t st) {
   const int n = pl.n * pl.G;
   if (n > 0)
-    gather_resp_rows_kernel<<<n, 256, 0, st>>>(pl, x, xc, d, (const char*)Q, (char*)Qc, ldq, ldqc, hq, qbytes);
+    gather_resp_rows_kernel<<<n, 256, 0, st>>>(pl, x, xc, d, (const char*)Q, (char*)Qc, ldq, ldqc, hq, qbytes, out_row);
 }
 
 __global__ void store_rows_kernel(int* a, int* b, I32Row va, I32Row vb, int n) {
@@ -470,26 +504,59 @@ void launch_store_rows(int* a, int* b, const I32Row& va, const I32Row& vb, int n
 
 // Prompt K / V of one sequence out of one layer of the cache: K rows
 // [off, off + P) of every head plane [Hkv][ld][hd] and the same key columns of
-// V^T [Hkv][hd][ld], both written as [Hkv][P][hd].
-template <class T>
-__global__ void read_cache_kernel(const T* __restrict__ K, const T* __restrict__ Vt, int ld, int off, int P,
-                                  int hkv, int hd, T* __restrict__ Kd, T* __restrict__ Vd) {
-  const size_t n = (size_t)hkv * P * hd;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const int e = (int)(i % hd);
-    const size_t r = i / hd;
-    const int p = (int)(r % P), h = (int)(r / P);
-    if (Kd) Kd[i] = K[((size_t)h * ld + off + p) * hd + e];
-    if (Vd) Vd[i] = Vt[((size_t)h * hd + e) * ld + off + p];
+// V^T [Hkv][hd][ld], both written as [Hkv][P][hd].  A block takes one head's
+// READ_KT keys; V^T goes through LDS, so that both its reads (along the keys)
+// and its writes (along the dimensions) are 16-byte chunks of whole lines.  One
+// element per thread, the V^T reads touched a line each: K and V of 4096 keys
+// x 32 heads (134 MB moved) took 37 + 84 us.
+// off and ld are multiples of 64 (the cache's own padding), so a tile's reads
+// stay inside the plane; VEC: the destination is 16-byte aligned.
+constexpr int READ_KT = 64;
+template <class T, bool VEC>
+__global__ __launch_bounds__(256) void read_cache_kernel(const T* __restrict__ K, const T* __restrict__ Vt, int ld,
+                                                         int off, int P, int hd, T* __restrict__ Kd,
+                                                         T* __restrict__ Vd) {
+  constexpr int CH = 16 / sizeof(T), PAD = CH;
+  __shared__ __attribute__((aligned(16))) T tile[READ_KT * (128 + PAD)];
+  const int h = blockIdx.y, p0 = blockIdx.x * READ_KT, np = min(READ_KT, P - p0);
+  const int nc = hd / CH, rs = hd + PAD;
+  // row r (key p0 + r), chunk c of a destination
+  auto put = [&](T* dst, int r, int c, uint4 v) {
+    T* p = dst + ((size_t)h * P + p0 + r) * hd + c * CH;
+    if constexpr (VEC) {
+      *(uint4*)p = v;
+    } else {
+      const T* e = (const T*)&v;
+#pragma unroll
+      for (int k = 0; k < CH; ++k) p[k] = e[k];
+    }
+  };
+  if (Kd) {
+    const T* src = K + ((size_t)h * ld + off + p0) * hd;
+    for (int i = threadIdx.x; i < np * nc; i += blockDim.x) put(Kd, i / nc, i % nc, *(const uint4*)(src + (size_t)i * CH));
+  }
+  if (Vd) {
+    constexpr int KC = READ_KT / CH;
+    for (int i = threadIdx.x; i < hd * KC; i += blockDim.x) {
+      const int d = i / KC, c = i % KC;
+      const uint4 v = *(const uint4*)(Vt + ((size_t)h * hd + d) * ld + off + p0 + c * CH);
+      const T* e = (const T*)&v;
+#pragma unroll
+      for (int k = 0; k < CH; ++k) tile[(c * CH + k) * rs + d] = e[k];
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < np * nc; i += blockDim.x) put(Vd, i / nc, i % nc, *(const uint4*)(tile + (i / nc) * rs + i % nc * CH));
   }
 }
 
 template <class T>
 void launch_read_cache(const void* K, const void* Vt, int ld, int off, int P, int hkv, int hd, void* Kd, void* Vd,
                        hipStream_t st) {
-  const size_t n = (size_t)hkv * P * hd;
-  const int blocks = (int)std::min<size_t>((n + 255) / 256, 4096);
-  read_cache_kernel<T><<<blocks, 256, 0, st>>>((const T*)K, (const T*)Vt, ld, off, P, hkv, hd, (T*)Kd, (T*)Vd);
+  const dim3 grid((P + READ_KT - 1) / READ_KT, hkv);
+  if ((((uintptr_t)Kd | (uintptr_t)Vd) & 15) == 0)
+    read_cache_kernel<T, true><<<grid, 256, 0, st>>>((const T*)K, (const T*)Vt, ld, off, P, hd, (T*)Kd, (T*)Vd);
+  else
+    read_cache_kernel<T, false><<<grid, 256, 0, st>>>((const T*)K, (const T*)Vt, ld, off, P, hd, (T*)Kd, (T*)Vd);
 }
 template void launch_read_cache<float>(const void*, const void*, int, int, int, int, int, void*, void*, hipStream_t);
 template void launch_read_cache<f16>(const void*, const void*, int, int, int, int, int, void*, void*, hipStream_t);

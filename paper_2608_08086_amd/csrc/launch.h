@@ -80,13 +80,14 @@ constexpr int ATTN_QT_F32 = 1;
 void launch_rope_table(float2* tab, int max_pos, int hd, double theta, hipStream_t st);
 // bf16 [rows][cols] row-major -> k-block-major (cols % 32 == 0)
 void launch_pack_kblock(const void* src, void* dst, int rows, int cols, hipStream_t st);
+// embedding rows, and their RMSNorm (gain, eps) into the activation (out, out2) laid out as act_at(row, k, ld, tiled)
 template <class T>
 void launch_embed(const SeqPlan& pl, const void* emb, int d, int V, int mask_id, const int* prompt,
-                  const int* resp, float* x, int* row_pos, int* row_dst, int* g_anchor, int* err,
-                  hipStream_t st);
+                  const int* resp, float* x, int* row_pos, int* row_dst, int* out_row, int* g_anchor, int* err,
+                  const float* gain, void* out, void* out2, int ld, int tiled, float eps, hipStream_t st);
 template <class T>
-void launch_rmsnorm(const SeqPlan& pl, int gather, int nrows, const float* x, const float* gain, void* out,
-                    void* out2, int ld, int tiled, int d, float eps, int* out_row, hipStream_t st);
+void launch_rmsnorm(int nrows, const float* x, const float* gain, void* out, void* out2, int ld, int tiled, int d,
+                    float eps, hipStream_t st);
 // Decision statistics: partials from stored logits (stat_col order, tiles of
 // BN columns, np = 2 ceil(V / BN) per row), then the per-row merge into
 // xhat (argmax), ell (log top probability) and qv (log p of the current token).
@@ -104,7 +105,7 @@ struct I32Row { int v[ARCHER_MAXB]; };
 void launch_store_rows(int* a, int* b, const I32Row& va, const I32Row& vb, int n, hipStream_t st);
 // FullForward response rows (residual, queries) into CachedForward row order
 void launch_gather_resp_rows(const SeqPlan& pl, const float* x, float* xc, int d, const void* Q, void* Qc, int ldq,
-                             int ldqc, int hq, int qbytes, hipStream_t st);
+                             int ldqc, int hq, int qbytes, int* out_row, hipStream_t st);
 template <class T>
 void launch_read_cache(const void* K, const void* Vt, int ld, int off, int P, int hkv, int hd, void* Kd, void* Vd,
                        hipStream_t st);
