@@ -494,23 +494,35 @@ int gemm_ksplit(int N, int K, int rows) {
 // one workgroup wherever the partial buffer holds the rows.
 static bool use_partials(const GemmArgs& a) { return a.ksplit > 1 && a.part && a.M <= a.part_rows; }
 
-// Time of one round of a one-slice launch's tiles (256 workgroups, one per CU)
-// in us at K 4096, measured on the LLaDA-8B projections with full rounds (the
-// ragged batch's 4096- and 24853-row passes; 768- and 4352-row passes order the
-// same way).  Two-term bf16 and single-term fp16 launches; 0: not a
-// configuration of the kind.
-static double tile_round_us(int cfg, bool f16) {
+// Time in us of a grid of a configuration's tiles over k of a K dimension: per
+// round of 256 workgroups (one per CU) a part that grows with k and TILE_US of
+// filling and draining.  Two-term bf16 and single-term fp16 launches; 0: not a
+// configuration of the kind.  Fitted to the LLaDA-8B and Dream-7B projections at 64
+// to 2048 rows and to the ragged batch's 4096- and 24853-row passes.  Two
+// workgroups of the 64-row tiles share a CU: further rounds cost less than the
+// first, and only one fill and drain shows (LLaDA-8B QKV in 64 x 192 tiles: 50 us
+// for 1 round, 124 for 3, 311 for 8; O at 1024 rows in 4 slices: 64 x 128 tiles
+// 84 us, 128 x 128 91).  A partly filled last round of 128 x 256 tiles is faster than
+// a full one (down of the Dream-7B shape, K 18944: 140 workgroups 326 us, 168 345,
+// 224 386); the other tiles showed no such gain.
+static double tiles_us(int cfg, bool f16, int grid, double k) {
+  const int rounds = (grid + 255) / 256;
+  constexpr double TILE_US = 5.0;
+  double t;   // per round and K 4096
   switch (cfg) {
-    case GEMM_NCFG + 1: return f16 ? 37.0 : 53.0;      // 128 x 128
-    case GEMM_NCFG + 0: return f16 ? 0.0 : 79.5;       // 128 x 192
-    case GEMM_NCFG + 2: return f16 ? 0.0 : 93.5;       // 128 x 256
-    case GEMM_NCFG + 3: return f16 ? 0.0 : 50.0;       // 64 x 192 (256 and 768 rows)
-    case GEMM_NCFG + 4: return f16 ? 0.0 : 37.0;       // 64 x 128 (120 to 768 rows: 33 to 39)
-    case GEMM_WIDE_128x192: return f16 ? 45.0 : 0.0;
-    case GEMM_WIDE_256x192: return f16 ? 75.0 : 140.0;
-    case GEMM_WIDE_256x256: return f16 ? 98.5 : 180.0;
-    default: return 0.0;
+    case GEMM_NCFG + 1: t = f16 ? 32.0 : 48.0; break;      // 128 x 128
+    case GEMM_NCFG + 0: t = f16 ? 0.0 : 75.0; break;       // 128 x 192
+    case GEMM_NCFG + 2: t = f16 ? 0.0 : 89.0; break;       // 128 x 256
+    case GEMM_NCFG + 3: t = f16 ? 0.0 : rounds == 1 ? 45.0 : 39.0; break;   // 64 x 192
+    case GEMM_NCFG + 4: t = f16 ? 0.0 : rounds == 1 ? 33.0 : 28.5; break;   // 64 x 128
+    case GEMM_WIDE_128x192: t = f16 ? 40.0 : 0.0; break;
+    case GEMM_WIDE_256x192: t = f16 ? 70.0 : 143.0; break;
+    case GEMM_WIDE_256x256: t = f16 ? 93.5 : 175.0; break;
+    default: t = 0.0;
   }
+  const bool shared = cfg == GEMM_NCFG + 3 || cfg == GEMM_NCFG + 4;
+  const double last = cfg == GEMM_NCFG + 2 ? 0.7 + 0.3 * (grid - (rounds - 1) * 256) / 256 : 1.0;
+  return t == 0.0 ? 0.0 : (rounds - 1 + last) * t * k / 4096 + (shared ? 1 : rounds) * TILE_US;
 }
 
 static void tile_size(int cfg, int* bm, int* bn) {
@@ -525,18 +537,16 @@ static bool one_slice_ok(int cfg, const GemmArgs& a, int epi) {
   return cfg >= GEMM_NCFG + GEMM_NCFG_LDS ? gemm_wide_ok(cfg, a, epi) : gemm_lds_cfg_ok(cfg - GEMM_NCFG, a);
 }
 
-// Rounds of 256 workgroups of a launch in S slices times the time of a round, in
-// us; 0: not a configuration of the kind.  The grid counts what the fullest XCD
-// gets of the tile order, eight times over.
-static double rounds_us(int cfg, const GemmArgs& a, int S) {
+// tiles_us of a launch in S slices; the grid counts what the fullest XCD gets of
+// the tile order, eight times over.
+static double launch_us(int cfg, const GemmArgs& a, int S) {
   int bm, bn;
   tile_size(cfg, &bm, &bn);
   const int grid = gemm_grid_size(a.N / bn, (a.M + bm - 1) / bm, S);
-  return (double)((grid + 255) / 256) * tile_round_us(cfg, a.f16 != 0) * a.K / 4096 / S;
+  return tiles_us(cfg, a.f16 != 0, grid, (double)a.K / S);
 }
 
-// The one-slice configuration with the least rounds times round time, and that
-// time in us; -1 if there is none.
+// The one-slice configuration with the least launch_us, and that time; -1 if there is none.
 static int one_slice_pick(const GemmArgs& a, int epi, double* cost) {
   int best = -1;
   for (int cfg : {(int)GEMM_WIDE_256x256, (int)GEMM_WIDE_256x192, GEMM_NCFG + 2, (int)GEMM_WIDE_128x192, GEMM_NCFG + 0,
@@ -544,7 +554,7 @@ static int one_slice_pick(const GemmArgs& a, int epi, double* cost) {
     int bm, bn;
     tile_size(cfg, &bm, &bn);
     if ((epi == EPI_STORE && bn != 256) || !one_slice_ok(cfg, a, epi)) continue;
-    const double c = rounds_us(cfg, a, 1);
+    const double c = launch_us(cfg, a, 1);
     if (c != 0.0 && (best < 0 || c < 0.98 * *cost)) { best = cfg; *cost = c; }
   }
   return best;
@@ -555,17 +565,16 @@ static int split_pick(const GemmArgs& a, double* cost) {
   int best = -1;
   for (int cfg : {GEMM_NCFG + 0, GEMM_NCFG + 1, GEMM_NCFG + 3, GEMM_NCFG + 4}) {
     if (!gemm_lds_cfg_ok(cfg - GEMM_NCFG, a)) continue;
-    const double c = rounds_us(cfg, a, a.ksplit);
+    const double c = launch_us(cfg, a, a.ksplit);
     if (best < 0 || c < 0.98 * *cost) { best = cfg; *cost = c; }
   }
   return best;
 }
 
 int gemm_pick_cfg(const GemmArgs& a, int epi) {
-  // One K slice with two-term or fp16 operands: the tile with the least rounds of 256 workgroups
-  // times the time of a round; of two within 2 % the wider one (so, for example,
-  // 256-row gate/up passes take 128 x 192 tiles, one round, 256-row QKV passes
-  // 128 x 128 tiles, and the 4096 rows of a serving batch 256 x 256 ones
+  // One K slice with two-term or fp16 operands: the tile with the least launch_us; of
+  // two within 2 % the wider one (so, for example, 256-row gate/up passes take
+  // 128 x 192 tiles, one round, 256-row QKV passes 64 x 192 tiles, and the 4096 rows of a serving batch 256 x 256 ones
   // throughout).  The LM head takes the column tile by N alone (256, when N has
   // at least 256 of them), so that the partials of its fused decision statistics
   // do not depend on the row count of a pass.
@@ -661,14 +670,14 @@ static int gemm_split_rows(const GemmArgs& a, int epi) {
   GemmArgs one = a;
   one.ksplit = 1;
   if (!gemm_wide_ok(GEMM_WIDE_256x256, one, epi)) return 0;
-  const double t = tile_round_us(GEMM_WIDE_256x256, a.f16 != 0) * a.K / 4096;
+  const auto wide = [&](int rounds) { return tiles_us(GEMM_WIDE_256x256, a.f16 != 0, rounds * 256, a.K); };
   // one launch of m rows in the context's slices
   const auto plain = [&](int m) {
     GemmArgs r = a;
     r.M = m;
     double c = 0.0;
     if (a.ksplit == 1) return one_slice_pick(r, epi, &c) >= 0 ? c : 1e30;
-    if (!a.A2 || split_pick(r, &c) < 0) c = rounds_us(GEMM_NCFG + 1, r, a.ksplit);
+    if (!a.A2 || split_pick(r, &c) < 0) c = launch_us(GEMM_NCFG + 1, r, a.ksplit);
     // the reduction reads the planes and the destination and writes it at about 4 TB/s
     return c + LAUNCH_US + (double)m * a.N * 4 * (a.ksplit + 2) / 4e6;
   };
@@ -680,7 +689,7 @@ static int gemm_split_rows(const GemmArgs& a, int epi) {
     int mt = (int)((long)r * 256 / nt);
     mt -= mt % tile_py(nt, mt);
     if (mt == 0 || gemm_grid_size(nt, mt, 1) > r * 256) continue;
-    const double c = r * t + (mt * 256 < a.M ? LAUNCH_US + plain(a.M - mt * 256) : 0.0);
+    const double c = wide(r) + (mt * 256 < a.M ? LAUNCH_US + plain(a.M - mt * 256) : 0.0);
     if (c < best) { best = c; m1 = mt * 256; }
   }
   return m1;
