@@ -449,7 +449,7 @@ void lds_rows64(const GemmArgs& a, bool partial, hipStream_t st) {
   if (partial) {
     gemm_lds_kernel<64, BN, 2, 2, 4, EPI, true, 2><<<grid, 512, 0, st>>>(a);
     launch_gemm_reduce(EPI, a, st);
-  } else if constexpr (EPI != EPI_STORE) {
+  } else {
     gemm_lds_kernel<64, BN, 2, 2, 4, EPI, true, 0><<<grid, 512, 0, st>>>(a);
   }
 }
@@ -472,7 +472,10 @@ void lds_epi(int c, const GemmArgs& a, bool partial, hipStream_t st) {
 
 }  // namespace
 
-int gemm_stats_bn(const GemmArgs& a) {
+int gemm_stats_bn(const GemmArgs& head) {
+  GemmArgs a = head;
+  float2 asked;
+  a.tstat = &asked;   // not read: the configuration of a launch with statistics
   // the configurations whose kernel is gemm_lds_kernel with a 2 x 2 wave grid
   const int cfg = gemm_pick_cfg(a, EPI_STORE) - GEMM_NCFG;
   if (cfg < 0 || a.ksplit != 1 || !gemm_lds_cfg_ok(cfg, a)) return 0;
@@ -499,7 +502,7 @@ int gemm_lds_tiles(int c, const GemmArgs& a) {
 int launch_gemm_lds_cfg(int epi, int c, bool partial, const GemmArgs& a, hipStream_t st) {
   if (!gemm_args_ok(epi, a) || !gemm_lds_cfg_ok(c, a)) return 1;
   if (partial && (!a.part || a.ksplit < 2)) return 1;
-  if (c >= 3 && !partial && (a.ksplit != 1 || epi == EPI_STORE)) return 1;
+  if (c >= 3 && !partial && (a.ksplit != 1 || a.tstat)) return 1;
   switch (epi) {
     case EPI_STORE: lds_epi<EPI_STORE>(c, a, partial, st); break;
     case EPI_RESID: lds_epi<EPI_RESID>(c, a, partial, st); break;

@@ -264,8 +264,8 @@ int wide_epi(int c, const GemmArgs& a, hipStream_t st) {
 
 bool gemm_wide_ok(int c, const GemmArgs& a, int epi) {
   // one K slice; two-term bf16 operands, or single-term fp16 ones (gate/up)
-  // (not the LM head: its statistics epilogue does not fit beside 256 accumulators)
-  if (epi == EPI_STORE || a.ksplit != 1 || (!a.A2 && !a.f16) || a.K % 64) return false;
+  // (no statistics epilogue: it does not fit beside 256 accumulators)
+  if ((epi == EPI_STORE && a.tstat) || a.ksplit != 1 || (!a.A2 && !a.f16) || a.K % 64) return false;
   // 32-bit lane offsets
   if ((size_t)a.N * (a.w_tiled ? BK : a.ldw) * 2 >= (1ull << 32) || (size_t)a.M * (a.a_tiled ? BK : a.lda) * 2 >= (1ull << 32))
     return false;
@@ -280,6 +280,7 @@ bool gemm_wide_ok(int c, const GemmArgs& a, int epi) {
 int launch_gemm_wide(int epi, int c, const GemmArgs& a, hipStream_t st) {
   if (!gemm_wide_ok(c, a, epi)) return 1;
   switch (epi) {
+    case EPI_STORE: return wide_epi<EPI_STORE>(c, a, st);
     case EPI_RESID: return wide_epi<EPI_RESID>(c, a, st);
     case EPI_SWIGLU: return wide_epi<EPI_SWIGLU>(c, a, st);
     case EPI_QKV: return wide_epi<EPI_QKV>(c, a, st);

@@ -116,3 +116,24 @@ def test_few_row_split_k_pass_matches_oracle(d, hq, hkv, hd, F, P, G):
     say(f"  max abs err full {err:.2e} cached {errc:.2e}")
     # the bound of the larger passes above, with the same operands
     assert err < 8e-3 and errc < 8e-3
+
+
+@pytest.mark.parametrize("V,B,G", [(4096, 16, 256), (4160, 11, 200), (8192, 17, 248)])
+def test_head_tiles_equal_single_passes(V, B, G):
+    """Logits of a batch's LM head (256 x 256 tiles without statistics; 4160 columns take the register-staged kernel;
+    ragged last row tiles) against each sequence alone, and the session's head with statistics against both."""
+    say(f"head V={V} rows={B * G}")
+    m = ModelShape(n_layers=1, d_model=4096, n_heads=2, n_kv_heads=2, head_dim=64, d_ff=128, vocab=V, dtype="bf16",
+                   init_std=0.02)
+    ctx = make_ctx(m, with_gains(model_weights(m, seed=11), 12), B, 8, 8 * B, G)
+    rng = np.random.default_rng(V)
+    prompt = dev_i32(rng.integers(0, m.mask_id, 8 * B))
+    g0 = dev_i32(np.where(rng.random((B, G)) < 0.5, m.mask_id, rng.integers(0, m.mask_id, (B, G))))
+    z = ctx.refresh_prompt(prompt, [8] * B, g0).clone()
+    assert bool(torch.isfinite(z).all())
+    for b in (0, B - 1):
+        alone = ctx.step(g0, seq_sel=[i == b for i in range(B)], logits=torch.full_like(z, 7.0))
+        full = ctx.refresh_prompt(prompt, [8] * B, g0, seq_sel=[i == b for i in range(B)], logits=torch.full_like(z, 7.0))
+        assert bool((full[b] == z[b]).all()), b
+        assert float((alone[b] - z[b]).abs().max()) < 8e-3, b   # keys from the cache: attention sums in another order
+        assert bool((alone[(b + 1) % B] == 7.0).all())
