@@ -11,8 +11,10 @@
 // fp32 partial, and a second kernel sums the partials in slice order and
 // applies the epilogue; or runs all slices in one workgroup, accumulating each
 // slice from zero and adding the slice sums in the same order.  Both give the
-// same bits, so a row's result never depends on how many rows are in the
-// launch (CachedForward on its own cache equals FullForward bitwise).
+// same bits, so a row's result does not depend on how many rows are in the
+// launch (CachedForward on its own cache equals FullForward bitwise), except
+// in passes so large that a split-K context runs whole rounds of CUs in one
+// slice (gemm_split_rows).
 //
 // Column pairing (gemm_common.h): tile column r and r + BN/2 are an RoPE or
 // SwiGLU pair, and each wave's columns are taken from both halves of the tile
@@ -474,13 +476,13 @@ int gemm_ksplit(int N, int K, int rows) {
   // GPU on its own (rows >= 2048: at least 16 row tiles); otherwise enough
   // slices that a 256-row launch of 128 x 128 tiles fills the 256 CUs,
   // within the K granularity.  The count is fixed per context (rows is the
-  // context's response-row capacity), never per launch, so every pass of a
-  // context sums every output in the same order.
+  // context's response-row capacity), never per launch: passes short of a whole
+  // round of wide tiles (gemm_split_rows) all sum in the same order.
   // A 256-row launch that already has three quarters of a round of 128 x 128
   // tiles (N >= 12288) also takes one slice: measured on the LLaDA-8B QKV
-  // projection, one slice is as fast as two at 256 rows (128 x 128 tiles)
-  // and 17 % faster in a 4352-row refresh pass (128 x 256 tiles, no partial
-  // planes or reduction).
+  // projection with 128 x 128 tiles, one slice is as fast as two at 256 rows
+  // (64 x 192 tiles then gain another 5 us) and needs no partial planes or
+  // reduction in a refresh pass.
   if (rows >= 2048) return 1;
   const int tiles = 2 * std::max(N / 128, 1);
   if (tiles >= 192) return 1;

@@ -47,9 +47,8 @@ void launch_pack_kblock(const void* src, void* dst, int rows, int cols, hipStrea
 // anchor g_r, in a cached pass (response rows only) the logits row.
 // Few rows are bound by the chain plan -> token -> row -> sum, so a row's elements go
 // four to a load where the table is aligned for it (VEC), and the norm's second
-// look at them hits the cache.  With the final norm run in the last reduction, the
-// two-layer LLaDA-8B cached step at prompt 512 went from 467 to 453 us; 24853
-// rows save one read of the residual.
+// look at them hits the cache: 256 rows of 4096 10 + 5 -> 7 us, 4096 rows (bound by
+// the bytes: one read of the residual less) 35 + 31 -> 47 us.
 template <class T, bool VEC>
 __global__ __launch_bounds__(NORM_THREADS) void embed_kernel(SeqPlan pl, const T* __restrict__ emb, int d, int V,
                                                              int mask_id, const int* __restrict__ prompt,
@@ -508,7 +507,7 @@ void launch_store_rows(int* a, int* b, const I32Row& va, const I32Row& vb, int n
 // READ_KT keys; V^T goes through LDS, so that both its reads (along the keys)
 // and its writes (along the dimensions) are 16-byte chunks of whole lines.  One
 // element per thread, the V^T reads touched a line each: K and V of 4096 keys
-// x 32 heads (134 MB moved) took 37 + 84 us.
+// x 32 heads (134 MB moved) took 37 + 84 us, of 512 keys 20 us where tiles take 11.
 // off and ld are multiples of 64 (the cache's own padding), so a tile's reads
 // stay inside the plane; VEC: the destination is 16-byte aligned.
 constexpr int READ_KT = 64;

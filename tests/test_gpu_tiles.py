@@ -73,13 +73,18 @@ def test_large_pass_of_split_k_context_matches_oracle(P, G):
     assert err < 8e-3 and errc < 8e-3
 
 
-@pytest.mark.parametrize("G,B", [(64, 32), (72, 29), (120, 18), (256, 8)])
-def test_few_row_pass_equals_batch_pass(G, B):
+@pytest.mark.parametrize("G,B,d,hq,hkv,F,layers", [
+    (64, 32, 128, 32, 32, 12288, 2),
+    (72, 29, 128, 32, 32, 12288, 2),
+    (120, 18, 128, 32, 32, 12288, 2),
+    (256, 8, 4096, 64, 4, 128, 1),     # QKV 64 x 192, with a tile that straddles the value heads
+])
+def test_few_row_pass_equals_batch_pass(G, B, d, hq, hkv, F, layers):
     """64-row tiles (one sequence alone: 64 x 128, at 256 rows 64 x 192 for QKV) give the bits of the batch's wide
     tiles; 72 and 120 rows leave a ragged last tile."""
-    say(f"few rows G={G} B={B}")
-    m = ModelShape(n_layers=2, d_model=128, n_heads=32, n_kv_heads=32, head_dim=128, d_ff=12288, vocab=512,
-                   dtype="bf16", gateup_fp16=False, init_std=0.05)
+    say(f"few rows G={G} B={B} d={d}")
+    m = ModelShape(n_layers=layers, d_model=d, n_heads=hq, n_kv_heads=hkv, head_dim=128, d_ff=F, vocab=512,
+                   dtype="bf16", gateup_fp16=False, init_std=0.05 if d < 1024 else 0.02)
     ctx = make_ctx(m, with_gains(model_weights(m, seed=3), 4), B, 8, 8 * B, G)
     rng = np.random.default_rng(G)
     g0 = rng.integers(0, m.mask_id, (B, G)).astype(np.int32)
