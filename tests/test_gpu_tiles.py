@@ -126,7 +126,7 @@ def test_few_row_split_k_pass_matches_oracle(d, hq, hkv, hd, F, P, G):
 @pytest.mark.parametrize("V,B,G", [(4096, 16, 256), (4160, 11, 200), (8192, 17, 248)])
 def test_head_tiles_equal_single_passes(V, B, G):
     """Logits of a batch's LM head (256 x 256 tiles without statistics; 4160 columns take the register-staged kernel;
-    ragged last row tiles) against each sequence alone, and the session's head with statistics against both."""
+    ragged last row tiles) against each sequence alone."""
     say(f"head V={V} rows={B * G}")
     m = ModelShape(n_layers=1, d_model=4096, n_heads=2, n_kv_heads=2, head_dim=64, d_ff=128, vocab=V, dtype="bf16",
                    init_std=0.02)
