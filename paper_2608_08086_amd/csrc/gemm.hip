@@ -341,12 +341,7 @@ __global__ __launch_bounds__(256) void gemm_reduce_qkv_kernel(GemmArgs a, int nv
     else if (dst_is_fresh(dst)) p = (Q*)a.Kf + ((size_t)(head - a.hq) * a.ldfresh + dst) * HD;
     else p = (Q*)a.Kc + ((size_t)(head - a.hq) * a.ldcache + dst_cache_row(dst)) * HD;
     f16x4 o1, o2;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float2 o = rope_rotate(v1[e], v2[e], cs[e]);
-      o1[e] = from_f32<Q>(o.x);
-      o2[e] = from_f32<Q>(o.y);
-    }
+    rope_rotate4(v1, v2, cs, &o1, &o2);
     *(f16x4*)(p + j) = o1;
     *(f16x4*)(p + j + HD / 2) = o2;
     return;

@@ -57,11 +57,53 @@ __device__ __forceinline__ void epi_swiglu(const GemmArgs& a, int row, int f, fl
   store_act<T>((T*)a.H, (T*)a.H2, act_at(row, f, a.ldh, a.h_tiled), silu_times(g, u));
 }
 
-// RoPE of one (first-half, second-half) dimension pair by (cos, sin); the
-// single definition used by every epilogue that rotates q/k.
-__device__ __forceinline__ float2 rope_rotate(float v1, float v2, float2 cs) {
-  // fused explicitly: the same bits in every kernel, whatever the compiler contracts
-  return make_float2(fmaf(v1, cs.x, -(v2 * cs.y)), fmaf(v2, cs.x, v1 * cs.y));
+// RoPE of (first-half, second-half) dimension pairs by (cos, sin):
+//   o1 = v1 cos - v2 sin,  o2 = v2 cos + v1 sin,
+// the product by sin rounded to fp32, the other one fused with the sum.  These
+// overloads are the only definition, so every kernel stores the same bits.  A
+// stored fp16 value is the fused result rounded once (v_fma_mix): written as an
+// fp32 expression and a conversion, it is rounded once or twice (to fp32, then
+// to fp16) as the compiler selects instructions, and about one value in 15000
+// differs.  The products by sin are plain expressions of v1 and v2, so the
+// compiler's own waits for those registers (MFMA results) stand before the
+// assembly; another instruction stands between the writes of a register's two
+// halves, and one behind the last, for the forwarding of partly written
+// registers.
+__device__ __forceinline__ void rope_rotate(float v1, float v2, float2 cs, float* o1, float* o2) {
+  *o1 = fmaf(v1, cs.x, -(v2 * cs.y));
+  *o2 = fmaf(v2, cs.x, v1 * cs.y);
+}
+
+__device__ __forceinline__ void rope_rotate(float v1, float v2, float2 cs, f16* o1, f16* o2) {
+  const float s1 = v2 * cs.y, s2 = v1 * cs.y;
+  unsigned r1, r2;
+  asm("v_fma_mixlo_f16 %0, %2, %4, -%5\n\t"
+      "v_fma_mixlo_f16 %1, %3, %4, %6\n\t"
+      "s_nop 0"
+      : "=&v"(r1), "=&v"(r2)
+      : "v"(v1), "v"(v2), "v"(cs.x), "v"(s1), "v"(s2));
+  *o1 = __builtin_bit_cast(f16, (unsigned short)r1);
+  *o2 = __builtin_bit_cast(f16, (unsigned short)r2);
+}
+
+// four consecutive pairs
+__device__ __forceinline__ void rope_rotate4(f32x4 v1, f32x4 v2, const float2* cs, f16x4* o1, f16x4* o2) {
+  unsigned r1[2], r2[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int e = 2 * h, f = e + 1;
+    const float2 ce = cs[e], cf = cs[f];
+    const float s1e = v2[e] * ce.y, s1f = v2[f] * cf.y, s2e = v1[e] * ce.y, s2f = v1[f] * cf.y;
+    asm("v_fma_mixlo_f16 %0, %2, %6, -%8\n\t"
+        "v_fma_mixlo_f16 %1, %4, %6, %10\n\t"
+        "v_fma_mixhi_f16 %0, %3, %7, -%9\n\t"
+        "v_fma_mixhi_f16 %1, %5, %7, %11\n\t"
+        "s_nop 0"
+        : "=&v"(r1[h]), "=&v"(r2[h])
+        : "v"(v1[e]), "v"(v1[f]), "v"(v2[e]), "v"(v2[f]), "v"(ce.x), "v"(cf.x), "v"(s1e), "v"(s1f), "v"(s2e), "v"(s2f));
+  }
+  *o1 = __builtin_bit_cast(f16x4, r1);
+  *o2 = __builtin_bit_cast(f16x4, r2);
 }
 
 // head in [0, hq + 2 hkv): q heads, k heads, v heads; v1 / v2 = dims j, j + hd/2
@@ -72,14 +114,14 @@ __device__ __forceinline__ void epi_qkv(const GemmArgs& a, int row, int head, in
   const int hd = a.hd;
   const int dst = a.row_dst[row];
   if (head < a.hq + a.hkv) {
-    const float2 o = rope_rotate(v1, v2, a.rope[(size_t)a.row_pos[row] * (hd / 2) + j]);
-    const float o1 = o.x, o2 = o.y;
+    Q o1, o2;
+    rope_rotate(v1, v2, a.rope[(size_t)a.row_pos[row] * (hd / 2) + j], &o1, &o2);
     Q* p;
     if (head < a.hq) p = (Q*)a.Qb + ((size_t)head * a.ldq + row) * hd;
     else if (dst_is_fresh(dst)) p = (Q*)a.Kf + ((size_t)(head - a.hq) * a.ldfresh + dst) * hd;
     else p = (Q*)a.Kc + ((size_t)(head - a.hq) * a.ldcache + dst_cache_row(dst)) * hd;
-    p[j] = from_f32<Q>(o1);
-    p[j + hd / 2] = from_f32<Q>(o2);
+    p[j] = o1;
+    p[j + hd / 2] = o2;
   } else {
     const int vh = head - a.hq - a.hkv;
     Q* vt;
@@ -165,12 +207,7 @@ __device__ __forceinline__ void epi_tile_pair4(const GemmArgs& a, int tile_n, in
       else if (dst_is_fresh(dst)) p = (Q*)a.Kf + ((size_t)(head - a.hq) * a.ldfresh + dst) * a.hd;
       else p = (Q*)a.Kc + ((size_t)(head - a.hq) * a.ldcache + dst_cache_row(dst)) * a.hd;
       f16x4 o1, o2;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float2 o = rope_rotate(v1[e], v2[e], cs[e]);
-        o1[e] = from_f32<Q>(o.x);
-        o2[e] = from_f32<Q>(o.y);
-      }
+      rope_rotate4(v1, v2, cs, &o1, &o2);
       *(f16x4*)(p + j) = o1;
       *(f16x4*)(p + j + half) = o2;
     } else {

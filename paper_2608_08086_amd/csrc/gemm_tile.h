@@ -185,13 +185,11 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& a, char* smem, int
         for (int cb = 0; cb < CB / 2; ++cb) {
           const int c = tc[cb] - lc + 4 * lg, j = c % half;
           f16* q = qs + r * RS + (c / half) * a.hd + j;
+          // copied here and not earlier: the accumulators may fill the accumulation registers
+          f32x4 v1 = acc[rb][cb], v2 = acc[rb][cb + CB / 2];
+          asm volatile("" : "+v"(v1), "+v"(v2));
           f16x4 o1, o2;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float2 o = rope_rotate(acc[rb][cb][e], acc[rb][cb + CB / 2][e], cs[j + e]);
-            o1[e] = from_f32<f16>(o.x);
-            o2[e] = from_f32<f16>(o.y);
-          }
+          rope_rotate4(v1, v2, cs + j, &o1, &o2);
           *(f16x4*)q = o1;
           *(f16x4*)(q + half) = o2;
         }
