@@ -11,10 +11,8 @@
 // fp32 partial, and a second kernel sums the partials in slice order and
 // applies the epilogue; or runs all slices in one workgroup, accumulating each
 // slice from zero and adding the slice sums in the same order.  Both give the
-// same bits, so a row's result does not depend on how many rows are in the
-// launch (CachedForward on its own cache equals FullForward bitwise), except
-// in passes so large that a split-K context runs whole rounds of CUs in one
-// slice (gemm_split_rows).
+// same bits, so a row's result never depends on how many rows are in the
+// launch (CachedForward on its own cache equals FullForward bitwise).
 //
 // Column pairing (gemm_common.h): tile column r and r + BN/2 are an RoPE or
 // SwiGLU pair, and each wave's columns are taken from both halves of the tile
@@ -471,8 +469,8 @@ int gemm_ksplit(int N, int K, int rows) {
   // GPU on its own (rows >= 2048: at least 16 row tiles); otherwise enough
   // slices that a 256-row launch of 128 x 128 tiles fills the 256 CUs,
   // within the K granularity.  The count is fixed per context (rows is the
-  // context's response-row capacity), never per launch: passes short of a whole
-  // round of wide tiles (gemm_split_rows) all sum in the same order.
+  // context's response-row capacity), never per launch, so every pass of a
+  // context sums every output in the same order.
   // A 256-row launch that already has three quarters of a round of 128 x 128
   // tiles (N >= 12288) also takes one slice: measured on the LLaDA-8B QKV
   // projection with 128 x 128 tiles, one slice is as fast as two at 256 rows
@@ -501,10 +499,12 @@ static bool use_partials(const GemmArgs& a) { return a.ksplit > 1 && a.part && a
 // for 1 round, 124 for 3, 311 for 8; O at 1024 rows in 4 slices: 64 x 128 tiles
 // 84 us, 128 x 128 91).  A partly filled last round of 128 x 256 tiles is faster than
 // a full one (down of the Dream-7B shape, K 18944: 140 workgroups 326 us, 168 345,
-// 224 386); the other tiles showed no such gain.
+// 224 386); the other tiles showed no such gain.  Folded slices (all of K in a tile,
+// in parts) cost FOLD_US a round: down of the LLaDA-8B shape, 4 slices, 335 us a round,
+// O 131.
 static double tiles_us(int cfg, bool f16, int grid, double k) {
   const int rounds = (grid + 255) / 256;
-  constexpr double TILE_US = 5.0;
+  constexpr double TILE_US = 5.0, FOLD_US = 20.0;
   double t;   // per round and K 4096
   switch (cfg) {
     case GEMM_NCFG + 1: t = f16 ? 32.0 : 48.0; break;      // 128 x 128
@@ -515,17 +515,19 @@ static double tiles_us(int cfg, bool f16, int grid, double k) {
     case GEMM_WIDE_128x192: t = f16 ? 40.0 : 0.0; break;
     case GEMM_WIDE_256x192: t = f16 ? 70.0 : 143.0; break;
     case GEMM_WIDE_256x256: t = f16 ? 93.5 : 175.0; break;
+    case GEMM_WIDE_FOLD_128x256: t = f16 ? 57.0 : 105.0; break;
     default: t = 0.0;
   }
   const bool shared = cfg == GEMM_NCFG + 3 || cfg == GEMM_NCFG + 4;
+  const double fill = cfg == GEMM_WIDE_FOLD_128x256 ? FOLD_US : TILE_US;
   const double last = cfg == GEMM_NCFG + 2 ? 0.7 + 0.3 * (grid - (rounds - 1) * 256) / 256 : 1.0;
-  return t == 0.0 ? 0.0 : (rounds - 1 + last) * t * k / 4096 + (shared ? 1 : rounds) * TILE_US;
+  return t == 0.0 ? 0.0 : (rounds - 1 + last) * t * k / 4096 + (shared ? 1 : rounds) * fill;
 }
 
 static void tile_size(int cfg, int* bm, int* bn) {
   const bool rows64 = cfg == GEMM_NCFG + 3 || cfg == GEMM_NCFG + 4;
   *bm = cfg == GEMM_WIDE_256x256 || cfg == GEMM_WIDE_256x192 ? 256 : rows64 ? 64 : 128;
-  *bn = cfg == GEMM_WIDE_256x256 || cfg == GEMM_NCFG + 2 ? 256
+  *bn = cfg == GEMM_WIDE_256x256 || cfg == GEMM_WIDE_FOLD_128x256 || cfg == GEMM_NCFG + 2 ? 256
         : cfg == GEMM_NCFG + 1 || cfg == GEMM_NCFG + 4   ? 128
                                                          : 192;
 }
@@ -652,36 +654,41 @@ int launch_gemm_bf16_cfg(int epi, int cfg, bool partial, const GemmArgs& a, hipS
   return 0;
 }
 
-// Rows [0, m1) of a launch that run as one-slice 256 x 256 tiles in whole rounds
-// of the 256 CUs, ahead of the rest with its own configuration; 0: one launch.
+// The tiles that whole rounds of CUs run in (gemm_split_rows).
+static int rounds_cfg(const GemmArgs& a) { return a.ksplit == 1 ? (int)GEMM_WIDE_256x256 : (int)GEMM_WIDE_FOLD_128x256; }
+
+// Rows [0, m1) of a launch that run as wide tiles in whole rounds of the 256
+// CUs, ahead of the rest with its own configuration; 0: one launch.
 //
 // A launch whose last round is nearly empty pays for a whole one: the 4352 rows
 // of a 4096-token refresh are 17 row tiles, 3.19 rounds of QKV tiles.  Rounds of
-// 16 row tiles and 256 rows apart took 553 + 53 us against 628, and O and down
-// (one round and 256 rows in split-K slices, 189 + 33 and 522 + 58 us) also drop
-// the partial planes of the large part: 275 + 89 and 724 + 93 us with every row
-// in 4 slices.  LAUNCH_US is the drain and start of the second launch.  Rows
-// of a split-K context then sum K in one slice or in several depending on
-// their place in a large pass (as attention splits its keys per pass); passes
-// short of a whole round, every cached pass of such a context, are not touched.
+// 16 row tiles and 256 rows apart took 553 + 53 us against 628.  Split-K launches run
+// their rounds in tiles that fold the slices, which saves the partial planes of
+// those rows and keeps the bits of separate slices: 4096 rows of O and down in 4
+// slices 262 + 37 and 668 + 65 us, for 400 to 435 and 826 to 873 with every row's
+// slices apart.  (One 256 x 256 tile over all of K takes 226 and 600, but then a
+// row's sums would depend on its place in the pass.)  LAUNCH_US is the drain and
+// start of the second launch.
 static int gemm_split_rows(const GemmArgs& a, int epi) {
   constexpr double LAUNCH_US = 8.0;
-  if (epi == EPI_STORE || !(a.A2 || a.f16) || a.N % 256) return 0;
-  GemmArgs one = a;
-  one.ksplit = 1;
-  if (!gemm_wide_ok(GEMM_WIDE_256x256, one, epi)) return 0;
-  const auto wide = [&](int rounds) { return tiles_us(GEMM_WIDE_256x256, a.f16 != 0, rounds * 256, a.K); };
+  const int cfg = rounds_cfg(a);
+  if (epi == EPI_STORE || !gemm_wide_ok(cfg, a, epi)) return 0;
+  int bm, bn;
+  tile_size(cfg, &bm, &bn);
+  const auto wide = [&](int rounds) { return tiles_us(cfg, a.f16 != 0, rounds * 256, a.K); };
   // one launch of m rows in the context's slices
   const auto plain = [&](int m) {
     GemmArgs r = a;
     r.M = m;
     double c = 0.0;
     if (a.ksplit == 1) return one_slice_pick(r, epi, &c) >= 0 ? c : 1e30;
+    // more rows than the partial buffer: 128 x 128 tiles that fold, 1.3 to 1.4 times a one-slice launch
+    if (!use_partials(r)) return 1.35 * launch_us(GEMM_NCFG + 1, r, 1);
     if (!a.A2 || split_pick(r, &c) < 0) c = launch_us(GEMM_NCFG + 1, r, a.ksplit);
     // the reduction reads the planes and the destination and writes it at about 4 TB/s
     return c + LAUNCH_US + (double)m * a.N * 4 * (a.ksplit + 2) / 4e6;
   };
-  const int nt = a.N / 256, mt_all = a.M / 256;
+  const int nt = a.N / bn, mt_all = a.M / bm;
   double best = 0.98 * plain(a.M);
   int m1 = 0;
   for (int r = 1; (long)r * 256 / nt <= mt_all; ++r) {
@@ -689,8 +696,8 @@ static int gemm_split_rows(const GemmArgs& a, int epi) {
     int mt = (int)((long)r * 256 / nt);
     mt -= mt % tile_py(nt, mt);
     if (mt == 0 || gemm_grid_size(nt, mt, 1) > r * 256) continue;
-    const double c = wide(r) + (mt * 256 < a.M ? LAUNCH_US + plain(a.M - mt * 256) : 0.0);
-    if (c < best) { best = c; m1 = mt * 256; }
+    const double c = wide(r) + (mt * bm < a.M ? LAUNCH_US + plain(a.M - mt * bm) : 0.0);
+    if (c < best) { best = c; m1 = mt * bm; }
   }
   return m1;
 }
@@ -700,7 +707,7 @@ bool gemm_fuses_norm(const GemmArgs& a) {
   return use_partials(a) && gemm_split_rows(a, EPI_RESID) == 0;
 }
 
-// The arguments of rows [r0, r0 + m) of a launch (r0 a multiple of 256).
+// The arguments of rows [r0, r0 + m) of a launch (r0 a multiple of 128).
 static GemmArgs gemm_rows(const GemmArgs& a, int r0, int m) {
   GemmArgs b = a;
   const auto act = [&](const void* p, int ld, int tiled) {
@@ -722,9 +729,7 @@ static GemmArgs gemm_rows(const GemmArgs& a, int r0, int m) {
 int launch_gemm_bf16(int epi, const GemmArgs& a, hipStream_t st) {
   if (!gemm_args_ok(epi, a)) return 1;
   if (const int m1 = gemm_split_rows(a, epi)) {
-    GemmArgs b = gemm_rows(a, 0, m1);
-    b.ksplit = 1;
-    const int rc = launch_gemm_wide(epi, GEMM_WIDE_256x256, b, st);
+    const int rc = launch_gemm_wide(epi, rounds_cfg(a), gemm_rows(a, 0, m1), st);
     if (rc || m1 == a.M) return rc;
     const GemmArgs c = gemm_rows(a, m1, a.M - m1);
     return launch_gemm_bf16_cfg(epi, gemm_pick_cfg(c, epi), use_partials(c), c, st);

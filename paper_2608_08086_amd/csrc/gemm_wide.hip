@@ -21,6 +21,11 @@
 // are pinned between MFMAs (at most one of each per pair), so that none comes
 // in a burst that would hold up the wave's next MFMA.
 //
+// FOLD tiles run the K slices of a split context one after the other, 128 x 256 so
+// that a second set of sums, the running total, fits beside the accumulators: the
+// bits of separate slices without their partial planes, for 112 us per 256 tiles
+// and K 4096 against 75 in half a 256 x 256 tile (gemm_split_rows says where).
+//
 // Addressing, stage layout and epilogues are those of gemm_lds.hip, and so are
 // the k order and the bits of every result.
 #include <algorithm>
@@ -29,7 +34,7 @@
 
 namespace {
 
-template <int BM, int BN, int WGM, int WGN, int NST, int EPI, bool SPLIT, bool F16 = false>
+template <int BM, int BN, int WGM, int WGN, int NST, int EPI, bool SPLIT, bool F16, bool FOLD>
 __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(GemmArgs a) {
   constexpr int WM = BM / WGM, WN = BN / WGN;
   constexpr int RB = WM / 16, CB = WN / 16;
@@ -122,6 +127,29 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(GemmArgs a) {
   };
   constexpr int T = RB * CB;   // MFMAs per term and k step
 
+  // FOLD: the K slices of a split context in order, each summed from zero and
+  // added to the running total, as the reduction of separate slices adds them
+  const int nslices = FOLD ? a.ksplit : 1, kt_slice = ntot / nslices;
+  f32x4 tot[FOLD ? RB : 1][FOLD ? CB : 1];
+  if constexpr (FOLD) {
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+      for (int j = 0; j < CB; ++j) tot[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  auto fold = [&]() __attribute__((always_inline)) {
+    if constexpr (FOLD) {
+#pragma unroll
+      for (int i = 0; i < RB; ++i)
+#pragma unroll
+        for (int j = 0; j < CB; ++j) {
+          tot[i][j] += acc[i][j];
+          acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+      settle();   // the zeros are written before the next slice's first product reads them
+    }
+  };
+
 #pragma unroll
   for (int s = 0; s < NST; ++s)
 #pragma unroll
@@ -167,10 +195,13 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(GemmArgs a) {
     };
     // every step alike, the last included (it refills from a clamped tile): no
     // product is issued outside the loop body
-    for (int g = 0, st = 0; g < ntot; ++g) {
-      const int stn = st + 1 == NST ? 0 : st + 1;
-      step(g, st, stn);
-      st = stn;
+    for (int sl = 0, g = 0, st = 0; sl < nslices; ++sl) {
+      for (const int end = g + kt_slice; g < end; ++g) {
+        const int stn = st + 1 == NST ? 0 : st + 1;
+        step(g, st, stn);
+        st = stn;
+      }
+      fold();
     }
   } else {
     bf16x8 fa[2][RB], fb[2][CB];
@@ -200,12 +231,15 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(GemmArgs a) {
       __builtin_amdgcn_sched_barrier(0);
     };
     // an even number of steps (K slices are multiples of 64): the fragment set is static
-    for (int g = 0, st = 0; g < ntot; g += 2) {
-      const int s1 = st + 1 == NST ? 0 : st + 1, s2 = s1 + 1 == NST ? 0 : s1 + 1;
-      step(g, st, s1, 0);
-      step(g + 1, s1, s2, 1);
-      settle();
-      st = s2;
+    for (int sl = 0, g = 0, st = 0; sl < nslices; ++sl) {
+      for (const int end = g + kt_slice; g < end; g += 2) {
+        const int s1 = st + 1 == NST ? 0 : st + 1, s2 = s1 + 1 == NST ? 0 : s1 + 1;
+        step(g, st, s1, 0);
+        step(g + 1, s1, s2, 1);
+        settle();
+        st = s2;
+      }
+      fold();
     }
   }
   __builtin_amdgcn_s_waitcnt(GL_VMCNT(0));   // the trailing loads land before the LDS is reused or released
@@ -215,8 +249,14 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(GemmArgs a) {
   for (int cb = 0; cb < CB; ++cb) tc[cb] = tcol(cb) + t0;
   // 256 x 256 QKV tiles leave no registers for the element-wise stores of a tile
   // that straddles the value heads: only launches without such tiles take them
-  tile_epilogue<BM, BN, WGN, RB, CB, EPI, EPI == EPI_QKV, false, NST * STAGE, 256, BM * BN == 65536>(
-      a, smem, tile_n, m0, wm, wn, lane, tid, tc, acc);
+  // (and even so two registers go through scratch memory between the loop and the stores)
+  constexpr bool QKV = EPI == EPI_QKV, ONLY_STAGED = BM * BN == 65536;
+  if constexpr (FOLD)
+    tile_epilogue<BM, BN, WGN, RB, CB, EPI, QKV, false, NST * STAGE, 256, ONLY_STAGED>(a, smem, tile_n, m0, wm, wn, lane,
+                                                                                       tid, tc, tot);
+  else
+    tile_epilogue<BM, BN, WGN, RB, CB, EPI, QKV, false, NST * STAGE, 256, ONLY_STAGED>(a, smem, tile_n, m0, wm, wn, lane,
+                                                                                       tid, tc, acc);
 }
 
 }  // namespace
@@ -224,10 +264,10 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(GemmArgs a) {
 
 namespace {
 
-template <int BM, int BN, int NST, int EPI, bool SPLIT, bool F16 = false>
+template <int BM, int BN, int NST, int EPI, bool SPLIT, bool F16 = false, bool FOLD = false>
 void wide(const GemmArgs& a, hipStream_t st) {
   const int grid = gemm_grid_size(a.N / BN, (a.M + BM - 1) / BM, 1);
-  gemm_wide_kernel<BM, BN, 2, 2, NST, EPI, SPLIT, F16><<<grid, 256, 0, st>>>(a);
+  gemm_wide_kernel<BM, BN, 2, 2, NST, EPI, SPLIT, F16, FOLD><<<grid, 256, 0, st>>>(a);
 }
 
 template <int EPI>
@@ -238,6 +278,13 @@ int wide_epi(int c, const GemmArgs& a, hipStream_t st) {
         if constexpr (EPI == EPI_SWIGLU) wide<256, 256, 4, EPI, false, true>(a, st);
       } else {
         wide<256, 256, 3, EPI, true>(a, st);
+      }
+      return 0;
+    case GEMM_WIDE_FOLD_128x256:
+      if (a.f16) {
+        if constexpr (EPI == EPI_SWIGLU) wide<128, 256, 4, EPI, false, true, true>(a, st);
+      } else {
+        if constexpr (EPI != EPI_STORE) wide<128, 256, 4, EPI, true, false, true>(a, st);
       }
       return 0;
     case GEMM_WIDE_256x192:
@@ -263,9 +310,10 @@ int wide_epi(int c, const GemmArgs& a, hipStream_t st) {
 }  // namespace
 
 bool gemm_wide_ok(int c, const GemmArgs& a, int epi) {
-  // one K slice; two-term bf16 operands, or single-term fp16 ones (gate/up)
+  // one K slice, or all slices folded; two-term bf16 operands, or single-term fp16 ones (gate/up)
   // (no statistics epilogue: it does not fit beside 256 accumulators)
-  if ((epi == EPI_STORE && a.tstat) || a.ksplit != 1 || (!a.A2 && !a.f16) || a.K % 64) return false;
+  if ((epi == EPI_STORE && a.tstat) || (!a.A2 && !a.f16) || a.ksplit < 1 || a.K % (64 * a.ksplit)) return false;
+  if ((a.ksplit > 1) != (c == GEMM_WIDE_FOLD_128x256)) return false;
   // 32-bit lane offsets
   if ((size_t)a.N * (a.w_tiled ? BK : a.ldw) * 2 >= (1ull << 32) || (size_t)a.M * (a.a_tiled ? BK : a.lda) * 2 >= (1ull << 32))
     return false;
@@ -273,6 +321,7 @@ bool gemm_wide_ok(int c, const GemmArgs& a, int epi) {
     case GEMM_WIDE_256x256: return a.N % 256 == 0 && (epi != EPI_QKV || qkv_all_staged(a, 256));
     case GEMM_WIDE_256x192: return a.N % 192 == 0 && (epi == EPI_SWIGLU || epi == EPI_QKV);
     case GEMM_WIDE_128x192: return a.N % 192 == 0 && epi == EPI_SWIGLU && a.f16;
+    case GEMM_WIDE_FOLD_128x256: return a.N % 256 == 0 && epi != EPI_STORE;
     default: return false;
   }
 }

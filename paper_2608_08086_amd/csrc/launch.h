@@ -115,11 +115,11 @@ void launch_read_act(const void* hi, const void* lo, int n, int d, int ld, int t
 // GEMM: returns 0 on success, nonzero if the shape is unsupported.
 // Configurations 0 .. GEMM_NCFG-1: register-staged kernel (gemm.hip);
 // GEMM_NCFG .. GEMM_NCFG+GEMM_NCFG_LDS-1: direct-to-LDS multistage kernel
-// (gemm_lds.hip); the GEMM_WIDE_ ones after them: wide tiles of one K slice
-// (gemm_wide.hip).  All give the same bits for the same (N, K) split.
+// (gemm_lds.hip); the GEMM_WIDE_ ones after them: wide tiles of one K slice,
+// _FOLD_ of all slices of a split launch (gemm_wide.hip).  All give the same bits for the same (N, K) split.
 constexpr int GEMM_NCFG = 7;
 constexpr int GEMM_NCFG_LDS = 5;
-enum { GEMM_WIDE_256x256 = GEMM_NCFG + GEMM_NCFG_LDS, GEMM_WIDE_256x192, GEMM_WIDE_128x192 };
+enum { GEMM_WIDE_256x256 = GEMM_NCFG + GEMM_NCFG_LDS, GEMM_WIDE_256x192, GEMM_WIDE_128x192, GEMM_WIDE_FOLD_128x256 };
 bool gemm_wide_ok(int c, const GemmArgs& a, int epi);
 int launch_gemm_wide(int epi, int c, const GemmArgs& a, hipStream_t st);
 int gemm_ksplit(int N, int K, int rows);

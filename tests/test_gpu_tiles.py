@@ -48,11 +48,38 @@ def test_batch_pass_equals_single_passes(d, hq, hkv, hd, F, fp16, B, G):
         assert bool((again[b] == z_full[b]).all()), b
 
 
+@pytest.mark.parametrize("d,hq,hkv,hd,F,fp16,B,P,G", [
+    (4096, 2, 2, 64, 128, True, 4, 1500, 256),      # O and down: 7024 rows together, 1756 alone
+    (4096, 2, 2, 64, 128, True, 3, 1390, 72),       # 4386 rows: a ragged rest
+    (1024, 8, 4, 128, 1024, True, 3, 1500, 256),    # QKV and fp16 gate/up: 5268 rows
+    (1024, 8, 8, 64, 1024, False, 3, 1536, 256),    # QKV of 64-dimension heads, two-term gate/up: 5376 rows
+])
+def test_split_k_refresh_does_not_depend_on_the_batch(d, hq, hkv, hd, F, fp16, B, P, G):
+    """In a context that splits K, a sequence refreshed in a pass of several whole rounds of CUs and
+    refreshed alone gets the same bits: logits, and the deepest layer's keys and values.  (Attention splits its
+    keys in both passes: fewer than 192 query tiles of 256 rows.)"""
+    say(f"split-K context, batch against alone d={d} heads={hq}/{hkv}x{hd} rows={B * (P + G)}")
+    m = ModelShape(n_layers=2, d_model=d, n_heads=hq, n_kv_heads=hkv, head_dim=hd, d_ff=F, vocab=256, dtype="bf16",
+                   gateup_fp16=fp16, init_std=0.02)
+    ctx = make_ctx(m, with_gains(model_weights(m, seed=8), 9), B, P, B * P, G)
+    rng = np.random.default_rng(P)
+    prompt = dev_i32(rng.integers(0, m.mask_id, B * P))
+    g0 = dev_i32(np.where(rng.random((B, G)) < 0.5, m.mask_id, rng.integers(0, m.mask_id, (B, G))))
+    z = ctx.refresh_prompt(prompt, [P] * B, g0).clone()
+    kv = [ctx.read_prompt_kv(1, b, P) for b in range(B)]
+    assert bool(torch.isfinite(z).all())
+    for b in range(B):
+        alone = ctx.refresh_prompt(prompt, [P] * B, g0, seq_sel=[i == b for i in range(B)], logits=torch.full_like(z, 7.0))
+        k, v = ctx.read_prompt_kv(1, b, P)
+        assert bool((k == kv[b][0]).all()) and bool((v == kv[b][1]).all()), b
+        assert bool((alone[b] == z[b]).all()), b
+
+
 @pytest.mark.parametrize("P,G", [(4100, 264), (3840, 256), (4090, 8)])
 def test_large_pass_of_split_k_context_matches_oracle(P, G):
-    """A context that splits K runs the whole rounds of a large refresh in one slice and only the
-    rest in slices (4364 rows: 4096 and a ragged 268; 4096 rows: no rest; 4098 rows: a rest of two
-    rows); its cached pass stays in slices."""
+    """A context that splits K folds the slices of a large refresh's whole rounds in the tile and gives
+    the rest's slices workgroups of their own (4364 rows: 4096 and a ragged 268; 4096 rows: no rest;
+    4098 rows: a rest of two rows), as in its cached pass."""
     say(f"split-K context P={P} G={G}")
     m = ModelShape(n_layers=2, d_model=4096, n_heads=2, n_kv_heads=2, head_dim=64, d_ff=128, vocab=256, dtype="bf16",
                    init_std=0.02)
