@@ -702,6 +702,8 @@ static int gemm_split_rows(const GemmArgs& a, int epi) {
   return m1;
 }
 
+// Whether launch_gemm_bf16 also runs the RMSNorm that a asks for: the launch has
+// one reduction for all its rows, whose kernel holds a row of up to 16 NORM_THREADS columns.
 bool gemm_fuses_norm(const GemmArgs& a) {
   if (!a.ngain || a.N % 4 || a.N > 16 * NORM_THREADS || a.ldx % 4 || a.ksplit > 8) return false;
   return use_partials(a) && gemm_split_rows(a, EPI_RESID) == 0;
@@ -726,8 +728,10 @@ static GemmArgs gemm_rows(const GemmArgs& a, int r0, int m) {
   return b;
 }
 
-int launch_gemm_bf16(int epi, const GemmArgs& a, hipStream_t st) {
-  if (!gemm_args_ok(epi, a)) return 1;
+int launch_gemm_bf16(int epi, const GemmArgs& a0, hipStream_t st) {
+  if (!gemm_args_ok(epi, a0)) return 1;
+  GemmArgs a = a0;
+  if (!gemm_fuses_norm(a)) a.ngain = nullptr;   // a plain reduction, of rows of any length
   if (const int m1 = gemm_split_rows(a, epi)) {
     const int rc = launch_gemm_wide(epi, rounds_cfg(a), gemm_rows(a, 0, m1), st);
     if (rc || m1 == a.M) return rc;

@@ -96,6 +96,37 @@ def test_small_bf16_full_and_cached(name):
     assert np.max(np.abs(zc - zc_ref)) < 2e-2
 
 
+@pytest.mark.parametrize("d", [8192, 8448])
+def test_split_k_rows_around_the_fused_norm_limit(d):
+    """The reduction that also normalises holds rows of up to 8192 columns; wider ones are
+    reduced and normalised apart."""
+    say(f"two-layer bf16 model, d {d}, split-K projections")
+    m = ModelShape(n_layers=2, d_model=d, n_heads=2, n_kv_heads=2, head_dim=64, d_ff=128, vocab=256, dtype="bf16",
+                   init_std=0.02)
+    W = with_gains(model_weights(m, seed=41), 41)
+    P, G = 21, 16
+    p = _prompt(m, P, 42)
+    ctx = make_ctx(m, W, 1, P, P, G)
+    g0, g1 = _resp(m, G, 43), _resp(m, G, 44, frac=0.6)
+    z = host(ctx.refresh_prompt(dev_i32(p), [P], dev_i32(g0[None])))[0]
+    x = host(ctx.read_rows(archer().READ_RESIDUAL, 1))
+    z_ref, cache, (hidden, _) = om.full_forward(W, m, p, g0, keep_hidden=True)
+    zc = host(ctx.step(dev_i32(g1[None])))[0]
+    xc = host(ctx.read_rows(archer().READ_RESIDUAL, 1))
+    zc_ref, (hidden_c, _) = om.cached_forward(W, m, g1, cache, P, keep_hidden=True)
+    # Every stored query, key, value and probability is an fp16 rounding, 2^-12 relative on average
+    # or less; four of them in a row, in two layers, in random directions: sqrt(8) 2^-12 of what the
+    # layers add to the residual, which grows at most as much again in the MLP's product.  Below 2^-9
+    # in the 2-norm; a missing update is an error of order 1 in its columns.
+    for got, want in ((x, hidden[-1][P:]), (xc, hidden_c[-1])):
+        for cols in (slice(0, 8192), slice(8192, d)):
+            if cols.start < d:
+                err = np.linalg.norm((got - want)[:, cols]) / np.linalg.norm(want[:, cols])
+                say(f"  residual columns from {cols.start}: relative error {err:.2e}")
+                assert err < 2.0**-9
+    assert np.max(np.abs(z - z_ref)) < 2e-2 and np.max(np.abs(zc - zc_ref)) < 2e-2
+
+
 @pytest.mark.parametrize("rows,cols,half", [(1, 32, False), (100, 96, False), (257, 4096, False),
                                             (100, 96, True)])
 def test_pack_weight_is_the_k_block_permutation(rows, cols, half):
