@@ -471,6 +471,8 @@ archer_status run_forward(archer_ctx* c, bool full, const std::vector<int>& sel,
     if (stats && c->stat_fused) {
       a.tstat = c->at<float2>(L.tstat); a.targ = c->at<int>(L.targ); a.zg = c->at<float>(L.zg);
       a.tg = resp; a.mask_id = m.mask_id;
+      // the merge of the partials reads c->np per row
+      if (gemm_stats_bn(a) != c->stat_tile) return fail(ARCHER_E_STATE, "the LM head's statistics tile has changed");
     } else if (!logits) {
       return fail(ARCHER_E_STATE, "a forward without logits needs the fused decision statistics");
     }

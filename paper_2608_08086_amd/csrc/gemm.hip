@@ -547,13 +547,10 @@ static double launch_us(int cfg, const GemmArgs& a, int S) {
 
 // The one-slice configuration with the least launch_us, and that time; -1 if there is none.
 static int one_slice_pick(const GemmArgs& a, int epi, double* cost) {
-  const bool stats = epi == EPI_STORE && a.tstat;
   int best = -1;
   for (int cfg : {(int)GEMM_WIDE_256x256, (int)GEMM_WIDE_256x192, GEMM_NCFG + 2, (int)GEMM_WIDE_128x192, GEMM_NCFG + 0,
                   GEMM_NCFG + 1, GEMM_NCFG + 3, GEMM_NCFG + 4}) {
-    int bm, bn;
-    tile_size(cfg, &bm, &bn);
-    if ((stats && (bm != 128 || bn != 256)) || !one_slice_ok(cfg, a, epi)) continue;
+    if (!one_slice_ok(cfg, a, epi)) continue;
     const double c = launch_us(cfg, a, 1);
     if (c != 0.0 && (best < 0 || c < 0.98 * *cost)) { best = cfg; *cost = c; }
   }
@@ -577,7 +574,8 @@ int gemm_pick_cfg(const GemmArgs& a, int epi) {
   // 128 x 192 tiles, one round, 256-row QKV passes 64 x 192 tiles, and the 4096 rows of a serving batch 256 x 256 ones
   // throughout).  An LM head that writes the decision statistics takes the column tile
   // by N alone (256, when N has at least 256 of them), so that their partials do not
-  // depend on the row count of a pass; one that only stores its logits is chosen
+  // depend on the row count of a pass or on the terms of its operands (which may change
+  // between the passes of a session); one that only stores its logits is chosen
   // like the others (16 x 256 rows of 4096 columns: one round of 256 x 256 tiles, 163 to
   // 180 us, for 216 in 128 x 128; 256 rows of the full vocabulary 480 for 495).
   // Two-term split-K launches choose the same way among the 128- and 64-row tiles
@@ -587,7 +585,8 @@ int gemm_pick_cfg(const GemmArgs& a, int epi) {
   // for slices folded in one workgroup (its second accumulator set does not
   // fit the registers of two waves per SIMD).
   const bool stats = epi == EPI_STORE && a.tstat;
-  if ((a.A2 || a.f16) && a.ksplit == 1 && (!stats || (a.N % 256 == 0 && a.N / 256 >= 256))) {
+  if (stats && a.N / 256 >= 256 && gemm_lds_cfg_ok(2, a)) return GEMM_NCFG + 2;
+  if (!stats && (a.A2 || a.f16) && a.ksplit == 1) {
     double cost;
     const int best = one_slice_pick(a, epi, &cost);
     if (best >= 0) return best;

@@ -429,7 +429,7 @@ struct LdsCfg { int BM, BN; };
 const LdsCfg kLds[GEMM_NCFG_LDS] = {
     {128, 192},   // 0: 2 x 2 multiply waves of 64 x 96, 4 stages
     {128, 128},   // 1: 2 x 2 multiply waves of 64 x 64, 4 stages
-    {128, 256},   // 2: 2 x 2 multiply waves of 64 x 128, 4 stages, one K slice, two-term
+    {128, 256},   // 2: 2 x 2 multiply waves of 64 x 128, 4 stages, one K slice, two-term (or an LM head's statistics)
     {64, 192},    // 3: 2 x 2 multiply waves of 32 x 96, 4 stages, two-term
     {64, 128},    // 4: 2 x 2 multiply waves of 32 x 64, 4 stages, two-term
 };
@@ -462,9 +462,13 @@ void lds_epi(int c, const GemmArgs& a, bool partial, hipStream_t st) {
     case 3: lds_rows64<192, EPI>(a, partial, st); break;
     case 4: lds_rows64<128, EPI>(a, partial, st); break;
     default: {
-      // one K slice of two-term activations (the in-place refill needs both terms)
+      // one K slice
       const int grid = gemm_grid_size(a.N / 256, (a.M + 127) / 128, 1);
-      gemm_lds_kernel<128, 256, 2, 2, 4, EPI, true, 0><<<grid, 512, 0, st>>>(a);
+      if (a.A2) {
+        gemm_lds_kernel<128, 256, 2, 2, 4, EPI, true, 0><<<grid, 512, 0, st>>>(a);
+      } else {
+        if constexpr (EPI == EPI_STORE) gemm_lds_kernel<128, 256, 2, 2, 4, EPI, false, 0><<<grid, 512, 0, st>>>(a);
+      }
       break;
     }
   }
@@ -486,7 +490,8 @@ bool gemm_lds_cfg_ok(int c, const GemmArgs& a) {
   if (c < 0 || c >= GEMM_NCFG_LDS) return false;
   const LdsCfg& k = kLds[c];
   if (a.M <= 0 || a.N % k.BN || a.ksplit < 1 || a.K % (a.ksplit * BK)) return false;
-  if (c == 2 && (!a.A2 || a.ksplit != 1)) return false;
+  // single-term launches only for the statistics, whose column tile must not depend on the terms
+  if (c == 2 && ((!a.A2 && !a.tstat) || a.ksplit != 1)) return false;
   if (c >= 3 && !a.A2) return false;
   // 32-bit lane offsets
   if ((size_t)a.N * (a.w_tiled ? BK : a.ldw) * 2 >= (1ull << 32) || (size_t)a.M * (a.a_tiled ? BK : a.lda) * 2 >= (1ull << 32))
@@ -502,6 +507,7 @@ int gemm_lds_tiles(int c, const GemmArgs& a) {
 int launch_gemm_lds_cfg(int epi, int c, bool partial, const GemmArgs& a, hipStream_t st) {
   if (!gemm_args_ok(epi, a) || !gemm_lds_cfg_ok(c, a)) return 1;
   if (partial && (!a.part || a.ksplit < 2)) return 1;
+  if (c == 2 && !a.A2 && epi != EPI_STORE) return 1;
   if (c >= 3 && !partial && (a.ksplit != 1 || a.tstat)) return 1;
   switch (epi) {
     case EPI_STORE: lds_epi<EPI_STORE>(c, a, partial, st); break;

@@ -215,3 +215,32 @@ def test_decide_statistics_of_stored_logits(V, B, G):
             assert out[0][b].tolist() == want.tolist()
     for x, y in zip(*outs):
         assert bool((x == y).all())
+
+
+@pytest.mark.parametrize("single", [(), ("head",), ("qkv", "o", "gateup", "down", "head")])
+def test_session_decides_as_the_single_calls(single):
+    """A session takes its statistics from the LM head's epilogue, the call-driven loop from the stored
+    logits: the same decisions, whatever terms the projections multiply.  65536 columns take the
+    256-column statistics tile."""
+    m = ModelShape(n_layers=1, d_model=128, n_heads=2, n_kv_heads=2, head_dim=64, d_ff=128, vocab=65536, dtype="bf16",
+                   init_std=0.1)
+    say(f"session against single calls, single-term {list(single)}")
+    a = archer()
+    W = with_gains(model_weights(m, seed=31), 31)
+    B, P, G, T, K = 2, [9, 14], 136, 24, 3
+    prompt = dev_i32(np.random.default_rng(32).integers(0, m.mask_id, sum(P)))
+    g0 = dev_i32(np.full((B, G), m.mask_id))
+    ctxs = [make_ctx(m, W, B, max(P), sum(P), G) for _ in range(2)]
+    for c in ctxs:
+        c.set_single_term(single)
+    out, tr = ctxs[0].decode(prompt, P, g0.clone(), policy=a.AGE, K=K, steps=T, k=2, tau=0.1)
+    g, r = g0, 0
+    z = ctxs[1].refresh_prompt(prompt, P, g)
+    for t in range(T):
+        g, dist, um, rm = ctxs[1].decide(z, g, k=2, tau=0.1, final=t == T - 1)
+        assert tr["unmask_pos"][t].tolist() == um.tolist() and tr["remask_pos"][t].tolist() == rm.tolist(), t
+        if t + 1 - r >= K:
+            z, r = ctxs[1].refresh_prompt(prompt, P, g), t + 1
+        else:
+            z = ctxs[1].step(g)
+    assert bool((out == g).all())
