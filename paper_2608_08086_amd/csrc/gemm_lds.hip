@@ -366,6 +366,16 @@ __global__ __launch_bounds__(512, 1) void gemm_lds_kernel(GemmArgs a) {
     // the last tile peeled off: no branch in the loop body
     for (int g = 0; g + 1 < ntot; ++g) tile_roll(g, true);
     tile_roll(ntot - 1, false);
+  } else if constexpr (PIPE1 && CB == 8) {
+    // no branch in the loop body: with 128 accumulators the copies of a body
+    // with branches do not fit the registers (K is a multiple of 64: gemm_lds_cfg_ok)
+    int g = 0;
+    for (; g + 2 < ntot; g += 2) {
+      tile_p1(g, 0, true);
+      tile_p1(g + 1, 1, true);
+    }
+    tile_p1(g, 0, true);
+    tile_p1(g + 1, 1, false);
   } else if constexpr (PIPE1) {
     for (int g = 0; g < ntot; g += 2) {           // fragment buffer parity static in the two halves
       tile_p1(g, 0, g + 1 < ntot);
@@ -491,7 +501,7 @@ bool gemm_lds_cfg_ok(int c, const GemmArgs& a) {
   const LdsCfg& k = kLds[c];
   if (a.M <= 0 || a.N % k.BN || a.ksplit < 1 || a.K % (a.ksplit * BK)) return false;
   // single-term launches only for the statistics, whose column tile must not depend on the terms
-  if (c == 2 && ((!a.A2 && !a.tstat) || a.ksplit != 1)) return false;
+  if (c == 2 && ((!a.A2 && (!a.tstat || a.K % 64)) || a.ksplit != 1)) return false;
   if (c >= 3 && !a.A2) return false;
   // 32-bit lane offsets
   if ((size_t)a.N * (a.w_tiled ? BK : a.ldw) * 2 >= (1ull << 32) || (size_t)a.M * (a.a_tiled ? BK : a.lda) * 2 >= (1ull << 32))
