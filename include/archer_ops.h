@@ -26,6 +26,17 @@ extern "C" {
 archer_status archer_op_gemm(int32_t dtype, int32_t M, int32_t N, int32_t K, const void *A,
                              const void *A_lo, const void *W, float *Y, void *hip_stream);
 
+/* The tiles that a projection of the model path takes, as text (host only, no
+ * GPU is touched): class k_class (ARCHER_K_GEMM_QKV, _O, _GATEUP, _DOWN or
+ * _HEAD; a full pass chooses like a cached one of as many rows) over `rows`
+ * rows in a context of this bf16 model and these limits, weights in `layout`,
+ * activations of the default precision; stats: the LM head also writes the
+ * decision statistics.  One part per launch, "<rows> rows [staged |wide ]<BM>x<BN>"
+ * with ", <S> slices" or ", <S> folded slices" where K is split, joined by
+ * "; ".  For checking that a shape reaches the kernel it is meant to. */
+archer_status archer_op_projection_tiles(const archer_model_cfg *cfg, const archer_limits *lim, int32_t layout,
+                                         int32_t k_class, int32_t rows, int32_t stats, char *text, size_t bytes);
+
 /* Non-causal attention of one sequence over two key segments, the anchored
  * attention of Eq. archer-attention: every query of head h attends to the nk1
  * keys of segment 1 followed by the nk2 keys of segment 2 of key/value head

@@ -37,7 +37,7 @@ EXPORTED = [
     "archer_op_attention_ws_bytes", "archer_op_attention", "archer_timing_begin", "archer_timing_end",
     "archer_pack_weight", "archer_session_begin", "archer_session_advance", "archer_session_response",
     "archer_session_state_bytes", "archer_session_save", "archer_session_restore", "archer_read_state",
-    "archer_set_single_term", "archer_op_attention_noalloc",
+    "archer_set_single_term", "archer_op_attention_noalloc", "archer_op_projection_tiles",
 ]
 FORWARD_CONTROLLER, FORWARD_REFRESH, FORWARD_CACHED = 0, 1, 2
 READ_LOGITS, READ_HIDDEN, READ_RESIDUAL, READ_PROMPT_K, READ_PROMPT_V = range(5)
@@ -131,6 +131,9 @@ lib.archer_set_single_term.argtypes = [P, C.c_uint32]
 lib.archer_op_attention_noalloc.restype = C.c_int
 lib.archer_op_attention_noalloc.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32, P, P, P,
                                             C.c_int32, C.c_int32, P, P, C.c_int32, C.c_int32, P, P]
+lib.archer_op_projection_tiles.restype = C.c_int
+lib.archer_op_projection_tiles.argtypes = [C.POINTER(ModelCfg), C.POINTER(Limits), C.c_int32, C.c_int32, C.c_int32,
+                                           C.c_int32, C.c_char_p, C.c_size_t]
 lib.archer_timing_begin.restype = C.c_int
 lib.archer_timing_begin.argtypes = [P, C.c_uint32, C.c_int32]
 lib.archer_timing_end.restype = C.c_int
@@ -169,6 +172,12 @@ def qkv_dtype(dtype: int):
     return torch.float16 if dtype == BF16 else torch.float32
 
 
+def _model_cfg(shape):
+    return ModelCfg(shape.n_layers, shape.d_model, shape.n_heads, shape.n_kv_heads, shape.head_dim, shape.d_ff,
+                    shape.vocab, shape.mask_id, shape.rms_eps, shape.rope_theta,
+                    BF16 if shape.dtype == "bf16" else FP32, int(bool(getattr(shape, "gateup_fp16", False))))
+
+
 class Context:
     """One archer_ctx: a model's weights (device tensors), limits and workspace."""
 
@@ -177,9 +186,7 @@ class Context:
         self.shape = shape
         self.dtype = BF16 if shape.dtype == "bf16" else FP32
         gu16 = int(bool(getattr(shape, "gateup_fp16", False)))
-        self.cfg = ModelCfg(shape.n_layers, shape.d_model, shape.n_heads, shape.n_kv_heads, shape.head_dim,
-                            shape.d_ff, shape.vocab, shape.mask_id, shape.rms_eps, shape.rope_theta, self.dtype,
-                            gu16)
+        self.cfg = _model_cfg(shape)
         want = torch.float16 if gu16 else torch_dtype(self.dtype)
         for L_ in weights["layers"]:
             for k in ("w_gate", "w_up"):
@@ -432,6 +439,15 @@ def op_gemm(A, Wt, dtype=BF16, A_lo=None):
     Y = torch.empty(M, N, dtype=torch.float32, device="cuda")
     _check(lib.archer_op_gemm(dtype, M, N, K, _ptr(A), _ptr(A_lo), _ptr(Wt), _ptr(Y), _stream()))
     return Y
+
+
+def projection_tiles(shape, limits, cls, rows, layout=LAYOUT_KBLOCK, stats=False):
+    """The tiles a projection class (K_GEMM_QKV .. K_GEMM_HEAD) over `rows` rows takes, as text; limits =
+    (max_batch, max_prompt_len, max_prompt_total, resp_len).  Host only."""
+    buf = C.create_string_buffer(256)
+    _check(lib.archer_op_projection_tiles(C.byref(_model_cfg(shape)), C.byref(Limits(*limits)), layout, cls, rows,
+                                          int(stats), buf, len(buf)))
+    return buf.value.decode()
 
 
 def op_attention(Q, K1, Vt1, nk1, K2, Vt2, nk2, dtype=BF16):

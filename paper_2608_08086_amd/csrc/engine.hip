@@ -272,16 +272,7 @@ SeqPlan build_plan(const archer_ctx* c, bool full, const std::vector<int>& sel) 
   return p;
 }
 
-// split-K slice count and partial buffer of a bf16 projection
-void gemm_prepare(archer_ctx* c, GemmArgs& a) {
-  if (!is_bf16(c)) return;
-  a.ksplit = gemm_ksplit(a.N, a.K, c->L.Rmax);
-  a.part = c->at<float>(c->L.part);
-  a.part_rows = c->L.part_rows;
-}
-
 archer_status gemm(archer_ctx* c, int cls, int epi, GemmArgs& a) {
-  gemm_prepare(c, a);
   const double es = (double)c->esz;
   double bytes = (double)a.M * a.K * es * (a.A2 ? 2 : 1) + (double)a.N * a.K * es;
   if (epi == EPI_STORE) bytes += (a.C ? (double)a.M * a.N * 4 : 0.0) + (a.tstat ? (double)a.M * c->np * 12 : 0.0);
@@ -303,6 +294,33 @@ GemmArgs gargs(const void* A, int lda, const void* W, int ldw, int M, int N, int
   return a;
 }
 
+// The shape of a projection (its cached-pass class) over `rows` rows and the layouts of its
+// operands, without pointers.  bf16 activations that feed a projection GEMM are stored
+// k-block-major with the buffer's row capacity as ld (act, O, H: Mmax rows; Cn: Rmax).
+GemmArgs proj_args(const archer_model_cfg& m, const Layout& L, int w_tiled, int cls, int rows) {
+  const int d = m.d_model, o = m.n_heads * m.head_dim, F = m.d_ff, qkv = (m.n_heads + 2 * m.n_kv_heads) * m.head_dim;
+  const bool tiled = m.dtype == ARCHER_BF16;
+  int N = 0, K = d, cap = L.Mmax, wrows = 0;
+  switch (cls) {
+    case ARCHER_K_GEMM_QKV: N = qkv; break;
+    case ARCHER_K_GEMM_O: N = d; K = o; break;
+    case ARCHER_K_GEMM_GATEUP: N = 2 * F; wrows = F; break;
+    case ARCHER_K_GEMM_DOWN: N = d; K = F; break;
+    default: N = m.vocab; cap = L.Rmax; break;   // ARCHER_K_GEMM_HEAD
+  }
+  GemmArgs a = gargs(nullptr, tiled ? cap : K, nullptr, w_tiled ? (wrows ? wrows : N) : K, rows, N, K);
+  a.a_tiled = tiled ? 1 : 0;
+  a.w_tiled = w_tiled;
+  a.f16 = cls == ARCHER_K_GEMM_GATEUP && tiled && m.gateup_fp16;
+  a.hq = m.n_heads; a.hkv = m.n_kv_heads; a.hd = m.head_dim;
+  a.ldq = L.ldq; a.ldcache = L.ldcache; a.ldfresh = L.ldfresh;
+  a.ldx = d;
+  a.ldh = tiled ? L.Mmax : F; a.h_tiled = a.a_tiled;
+  a.ldc = m.vocab;
+  if (tiled) { a.ksplit = gemm_ksplit(N, K, L.Rmax); a.part_rows = L.part_rows; }
+  return a;
+}
+
 // One forward over the selected sequences (full = FullForward, else CachedForward).
 // stats: the LM head also writes the decision statistics partials of the
 // response rows (contexts with stat_fused); logits may then be null.
@@ -312,7 +330,7 @@ archer_status run_forward(archer_ctx* c, bool full, const std::vector<int>& sel,
   const archer_model_cfg& m = c->cfg;
   const Layout& L = c->L;
   const SeqPlan pl = build_plan(c, full, sel);
-  const int d = m.d_model, hq = m.n_heads, hkv = m.n_kv_heads, hd = m.head_dim, F = m.d_ff;
+  const int d = m.d_model, hq = m.n_heads, hkv = m.n_kv_heads, hd = m.head_dim;
   // The layers run on plan P over R rows with residual X; in a full pass the
   // last layer switches to the CachedForward plan of the same sequences after
   // its QKV projection: the prompt rows' keys and values are then in the cache
@@ -320,7 +338,6 @@ archer_status run_forward(archer_ctx* c, bool full, const std::vector<int>& sel,
   const SeqPlan plc = full ? build_plan(c, false, sel) : pl;
   const SeqPlan* P = &pl;
   int rows = pl.rows;
-  const int qkv_n = (hq + 2 * hkv) * hd;
   const size_t es = c->esz;
   float* x = c->at<float>(L.x);
   void* qbuf = c->at<char>(L.Q);
@@ -341,9 +358,7 @@ archer_status run_forward(archer_ctx* c, bool full, const std::vector<int>& sel,
   int* row_dst = c->at<int>(L.row_dst);
   archer_status st;
 
-  // bf16 activations that feed a projection GEMM are stored k-block-major
-  // with the buffer's row capacity as ld (act, O, H: Mmax rows; Cn: Rmax)
-  const int tiled = is_bf16(c) ? 1 : 0;
+  const int tiled = is_bf16(c) ? 1 : 0;   // activation layout, see proj_args
   // the embedding rows and, from them, the first layer's attn_norm
   st = timed(c, ARCHER_K_EMBED, (double)rows * d * (es * (act2_qkv ? 3 : 2) + 4), 0.0, [&] {
     int* out_row = c->at<int>(L.out_row);
@@ -378,6 +393,13 @@ archer_status run_forward(archer_ctx* c, bool full, const std::vector<int>& sel,
     return v;
   };
 
+  const auto proj = [&](int cls, const void* A, const void* A2, const void* W) {
+    GemmArgs a = proj_args(m, L, c->w_tiled, cls, rows);
+    a.A = A; a.A2 = A2; a.W = W;
+    if (tiled) a.part = c->at<float>(L.part);
+    return a;
+  };
+
   // RMSNorms whose input is the residual just updated by a split-K GEMM run
   // inside that GEMM's reduction (same arithmetic as the stand-alone kernel)
   auto fuse_norm = [&](GemmArgs& a, const float* gain, void* out, void* out2, int ld, bool half = false) {
@@ -390,14 +412,11 @@ archer_status run_forward(archer_ctx* c, bool full, const std::vector<int>& sel,
     if (!normed && (st = norm(c->attn_norm[l], rows, act, act2_qkv, L.Mmax))) return st;
     normed = false;
     {
-      GemmArgs a = gargs(act, tiled ? L.Mmax : d, c->w_qkv[l], c->w_tiled ? qkv_n : d, rows, qkv_n, d);
-      a.A2 = act2_qkv; a.a_tiled = tiled; a.w_tiled = c->w_tiled;
-      a.Qb = c->at<char>(L.Q); a.ldq = L.ldq;
+      GemmArgs a = proj(ARCHER_K_GEMM_QKV, act, act2_qkv, c->w_qkv[l]);
+      a.Qb = c->at<char>(L.Q);
       a.Kc = c->at<char>(L.Kc) + (size_t)l * L.cache_layer_elems * es;
       a.Vtc = c->at<char>(L.Vtc) + (size_t)l * L.cache_layer_elems * es;
-      a.ldcache = L.ldcache;
-      a.Kf = c->at<char>(L.Kf); a.Vtf = c->at<char>(L.Vtf); a.ldfresh = L.ldfresh;
-      a.hq = hq; a.hkv = hkv; a.hd = hd;
+      a.Kf = c->at<char>(L.Kf); a.Vtf = c->at<char>(L.Vtf);
       a.row_pos = row_pos; a.row_dst = row_dst; a.rope = c->at<float2>(L.rope);
       if ((st = gemm(c, full ? ARCHER_K_GEMM_QKV_FULL : ARCHER_K_GEMM_QKV, EPI_QKV, a))) return st;
     }
@@ -433,10 +452,8 @@ archer_status run_forward(archer_ctx* c, bool full, const std::vector<int>& sel,
       if (st) return st;
     }
     {
-      GemmArgs a = gargs(c->at<char>(L.O), tiled ? L.Mmax : hq * hd, c->w_o[l], c->w_tiled ? d : hq * hd, rows,
-                         d, hq * hd);
-      a.A2 = o2; a.a_tiled = tiled; a.w_tiled = c->w_tiled;
-      a.X = x; a.ldx = d;
+      GemmArgs a = proj(ARCHER_K_GEMM_O, c->at<char>(L.O), o2, c->w_o[l]);
+      a.X = x;
       fuse_norm(a, c->mlp_norm[l], act, act2_mlp, L.Mmax, mlp16);
       if ((st = gemm(c, full ? ARCHER_K_GEMM_O_FULL : ARCHER_K_GEMM_O, EPI_RESID, a))) return st;
       normed = gemm_fuses_norm(a);
@@ -444,16 +461,14 @@ archer_status run_forward(archer_ctx* c, bool full, const std::vector<int>& sel,
     if (!normed && (st = norm(c->mlp_norm[l], rows, act, act2_mlp, L.Mmax, mlp16))) return st;
     normed = false;
     {
-      GemmArgs a = gargs(act, tiled ? L.Mmax : d, c->w_gate[l], c->w_tiled ? F : d, rows, 2 * F, d);
-      a.A2 = act2_mlp; a.a_tiled = tiled; a.w_tiled = c->w_tiled; a.f16 = mlp16 ? 1 : 0;
+      GemmArgs a = proj(ARCHER_K_GEMM_GATEUP, act, act2_mlp, c->w_gate[l]);
       a.W2 = c->w_up[l];
-      a.H = c->at<char>(L.H); a.H2 = h2; a.ldh = tiled ? L.Mmax : F; a.h_tiled = tiled;
+      a.H = c->at<char>(L.H); a.H2 = h2;
       if ((st = gemm(c, full ? ARCHER_K_GEMM_GATEUP_FULL : ARCHER_K_GEMM_GATEUP, EPI_SWIGLU, a))) return st;
     }
     {
-      GemmArgs a = gargs(c->at<char>(L.H), tiled ? L.Mmax : F, c->w_down[l], c->w_tiled ? d : F, rows, d, F);
-      a.A2 = h2; a.a_tiled = tiled; a.w_tiled = c->w_tiled;
-      a.X = x; a.ldx = d;
+      GemmArgs a = proj(ARCHER_K_GEMM_DOWN, c->at<char>(L.H), h2, c->w_down[l]);
+      a.X = x;
       // the rows after the last layer are the response rows in the LM head's order
       if (l + 1 < m.n_layers) fuse_norm(a, c->attn_norm[l + 1], act, act2_qkv, L.Mmax);
       else fuse_norm(a, c->final_norm, c->at<char>(L.Cn), cn2, L.Rmax);
@@ -461,13 +476,11 @@ archer_status run_forward(archer_ctx* c, bool full, const std::vector<int>& sel,
       normed = gemm_fuses_norm(a);
     }
   }
-  const int nresp = pl.n * pl.G;
-  if (!normed && (st = norm(c->final_norm, nresp, c->at<char>(L.Cn), cn2, L.Rmax))) return st;
+  // the rows are the response rows by now
+  if (!normed && (st = norm(c->final_norm, rows, c->at<char>(L.Cn), cn2, L.Rmax))) return st;
   {
-    GemmArgs a = gargs(c->at<char>(L.Cn), tiled ? L.Rmax : d, c->lm_head, c->w_tiled ? m.vocab : d, nresp,
-                       m.vocab, d);
-    a.A2 = cn2; a.a_tiled = tiled; a.w_tiled = c->w_tiled;
-    a.C = logits; a.ldc = m.vocab; a.out_row = c->at<int>(L.out_row);
+    GemmArgs a = proj(ARCHER_K_GEMM_HEAD, c->at<char>(L.Cn), cn2, c->lm_head);
+    a.C = logits; a.out_row = c->at<int>(L.out_row);
     if (stats && c->stat_fused) {
       a.tstat = c->at<float2>(L.tstat); a.targ = c->at<int>(L.targ); a.zg = c->at<float>(L.zg);
       a.tg = resp; a.mask_id = m.mask_id;
@@ -702,11 +715,8 @@ archer_status archer_init(const archer_model_cfg* cfg, const archer_weights* w, 
   }
   if (cfg->dtype == ARCHER_BF16) {
     // the LM head of a full batch of response rows, as run_forward launches it
-    GemmArgs h = gargs(c->at<char>(L.Cn), L.Rmax, c->lm_head, c->w_tiled ? cfg->vocab : cfg->d_model, L.Rmax,
-                       cfg->vocab, cfg->d_model);
-    h.A2 = c->at<char>(L.Cn2); h.a_tiled = 1; h.w_tiled = c->w_tiled;
-    h.ksplit = gemm_ksplit(cfg->vocab, cfg->d_model, L.Rmax);
-    h.C = c->at<float>(L.logits); h.ldc = cfg->vocab;
+    GemmArgs h = proj_args(*cfg, L, c->w_tiled, ARCHER_K_GEMM_HEAD, L.Rmax);
+    h.A = c->at<char>(L.Cn); h.A2 = c->at<char>(L.Cn2); h.W = c->lm_head; h.C = c->at<float>(L.logits);
     const int bn = gemm_stats_bn(h);
     c->stat_fused = bn > 0;
     if (bn > 0) c->stat_tile = bn;
@@ -1089,6 +1099,35 @@ archer_status archer_op_gemm(int32_t dtype, int32_t M, int32_t N, int32_t K, con
   else return fail(ARCHER_E_ARG, "bad dtype");
   if (rc) return fail(ARCHER_E_UNSUPPORTED, "gemm shape unsupported");
   HIPCHK(hipGetLastError());
+  return ARCHER_OK;
+}
+
+archer_status archer_op_projection_tiles(const archer_model_cfg* cfg, const archer_limits* lim, int32_t layout,
+                                         int32_t k_class, int32_t rows, int32_t stats, char* text, size_t bytes) {
+  const std::string e = check_cfg(cfg, lim);
+  if (!e.empty()) return fail(ARCHER_E_UNSUPPORTED, e);
+  if (cfg->dtype != ARCHER_BF16) return fail(ARCHER_E_UNSUPPORTED, "the tiles of fp32 projections follow from the shape alone");
+  if (layout != ARCHER_LAYOUT_ROWMAJOR && layout != ARCHER_LAYOUT_KBLOCK) return fail(ARCHER_E_ARG, "unknown weight layout");
+  int epi;
+  switch (k_class) {
+    case ARCHER_K_GEMM_QKV: epi = EPI_QKV; break;
+    case ARCHER_K_GEMM_O: case ARCHER_K_GEMM_DOWN: epi = EPI_RESID; break;
+    case ARCHER_K_GEMM_GATEUP: epi = EPI_SWIGLU; break;
+    case ARCHER_K_GEMM_HEAD: epi = EPI_STORE; break;
+    default: return fail(ARCHER_E_ARG, "k_class is not a projection of a cached pass");
+  }
+  const Layout L = make_layout(cfg, lim);
+  if (rows < 1 || rows > (epi == EPI_STORE ? L.Rmax : L.Mmax)) return fail(ARCHER_E_SHAPE, "rows beyond the limits");
+  if (!text || bytes == 0) return fail(ARCHER_E_ARG, "null text");
+  // the choice reads which operands there are and how they are aligned, never what they point to
+  GemmArgs a = proj_args(*cfg, L, layout == ARCHER_LAYOUT_KBLOCK, k_class, rows);
+  char* p = (char*)256;
+  a.A = p; a.A2 = a.f16 ? nullptr : p; a.W = p; a.W2 = p; a.part = (float*)p; a.C = (float*)p; a.X = (float*)p;
+  a.H = p; a.H2 = p; a.Qb = p; a.Kf = p; a.Vtf = p; a.Kc = p; a.Vtc = p;
+  if (epi == EPI_STORE && stats) a.tstat = (float2*)p;
+  const std::string t = gemm_route_text(epi, a);
+  if (t.size() >= bytes) return fail(ARCHER_E_ARG, "text too small");
+  memcpy(text, t.c_str(), t.size() + 1);
   return ARCHER_OK;
 }
 

@@ -26,6 +26,7 @@
 // through its L2 (with 8 slices each XCD owns one K slice, whose part of A
 // stays in its L2).
 #include <algorithm>
+#include <string>
 
 #include "launch.h"
 
@@ -727,17 +728,48 @@ static GemmArgs gemm_rows(const GemmArgs& a, int r0, int m) {
   return b;
 }
 
+// How a launch runs: rows [0, m1) in rounds_cfg tiles, the others in configuration
+// cfg (no others when m1 is M), their slices in workgroups of their own or not.
+namespace {
+struct GemmRoute { int m1, cfg; bool partial; };
+}  // namespace
+
+static GemmRoute gemm_route(int epi, const GemmArgs& a) {
+  GemmRoute r{gemm_split_rows(a, epi), 0, false};
+  if (r.m1 < a.M) {
+    const GemmArgs rest = gemm_rows(a, r.m1, a.M - r.m1);
+    r.cfg = gemm_pick_cfg(rest, epi);
+    r.partial = use_partials(rest);
+  }
+  return r;
+}
+
 int launch_gemm_bf16(int epi, const GemmArgs& a0, hipStream_t st) {
   if (!gemm_args_ok(epi, a0)) return 1;
   GemmArgs a = a0;
   if (!gemm_fuses_norm(a)) a.ngain = nullptr;   // a plain reduction, of rows of any length
-  if (const int m1 = gemm_split_rows(a, epi)) {
-    const int rc = launch_gemm_wide(epi, rounds_cfg(a), gemm_rows(a, 0, m1), st);
-    if (rc || m1 == a.M) return rc;
-    const GemmArgs c = gemm_rows(a, m1, a.M - m1);
-    return launch_gemm_bf16_cfg(epi, gemm_pick_cfg(c, epi), use_partials(c), c, st);
-  }
-  return launch_gemm_bf16_cfg(epi, gemm_pick_cfg(a, epi), use_partials(a), a, st);
+  const GemmRoute r = gemm_route(epi, a);
+  if (r.m1 == 0) return launch_gemm_bf16_cfg(epi, r.cfg, r.partial, a, st);
+  const int rc = launch_gemm_wide(epi, rounds_cfg(a), gemm_rows(a, 0, r.m1), st);
+  if (rc || r.m1 == a.M) return rc;
+  return launch_gemm_bf16_cfg(epi, r.cfg, r.partial, gemm_rows(a, r.m1, a.M - r.m1), st);
+}
+
+std::string gemm_route_text(int epi, const GemmArgs& a) {
+  const auto part = [&](int rows, int cfg, bool partial) {
+    int bm, bn;
+    if (cfg < GEMM_NCFG) { bm = kCfgBM[cfg]; bn = kCfgBN[cfg]; }
+    else tile_size(cfg, &bm, &bn);
+    std::string t = std::to_string(rows) + " rows " + (cfg < GEMM_NCFG ? "staged " : cfg >= GEMM_NCFG + GEMM_NCFG_LDS ? "wide " : "") +
+                    std::to_string(bm) + "x" + std::to_string(bn);
+    if (a.ksplit > 1) t += ", " + std::to_string(a.ksplit) + (partial ? " slices" : " folded slices");
+    return t;
+  };
+  const GemmRoute r = gemm_route(epi, a);
+  std::string t;
+  if (r.m1) t = part(r.m1, rounds_cfg(a), false);
+  if (r.m1 < a.M) t += (r.m1 ? "; " : "") + part(a.M - r.m1, r.cfg, r.partial);
+  return t;
 }
 
 // ---------------------------------------------------------------------------

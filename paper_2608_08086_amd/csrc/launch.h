@@ -131,6 +131,7 @@ int gemm_grid_size(int n_tiles, int m_tiles, int S);
 int gemm_pick_cfg(const GemmArgs& a, int epi);
 int launch_gemm_bf16_cfg(int epi, int cfg, bool partial, const GemmArgs& a, hipStream_t st);
 int launch_gemm_bf16(int epi, const GemmArgs& a, hipStream_t st);
+std::string gemm_route_text(int epi, const GemmArgs& a);   // the tiles launch_gemm_bf16 takes
 // Column tile of the LM-head GEMM when it can also produce the decision
 // statistics partials (bf16, one slice, a 2 x 2 wave grid), else 0.
 int gemm_stats_bn(const GemmArgs& a);

@@ -87,6 +87,17 @@ def test_workspace_bytes_and_host_side_errors():
     # shape checks happen on the host before any launch (N not a multiple of 64)
     assert archer.lib.archer_op_gemm(archer.BF16, 8, 60, 64, C.c_void_p(16), None, C.c_void_p(16),
                                      C.c_void_p(16), None) == archer.E_SHAPE
+    # the tiles of a projection: host only, refused for what the model path would refuse
+    lim16 = archer.Limits(16, 64, 1024, 256)
+    buf = C.create_string_buffer(64)
+    tiles = lambda cfg, cls, rows, n=64: archer.lib.archer_op_projection_tiles(  # noqa: E731
+        C.byref(cfg), C.byref(lim16), archer.LAYOUT_KBLOCK, cls, rows, 0, buf, n)
+    bf = _cfg(archer, dtype=archer.BF16)
+    assert tiles(bf, archer.K_GEMM_O, 5120) == archer.OK and buf.value.startswith(b"5120 rows ")
+    assert tiles(bf, archer.K_GEMM_O, 5121) == archer.E_SHAPE and tiles(bf, archer.K_GEMM_HEAD, 4097) == archer.E_SHAPE
+    assert tiles(bf, archer.K_GEMM_O, 0) == archer.E_SHAPE and tiles(bf, archer.K_ATTN, 8) == archer.E_ARG
+    assert tiles(bf, archer.K_GEMM_O, 8, 4) == archer.E_ARG
+    assert tiles(_cfg(archer), archer.K_GEMM_O, 8) == archer.E_UNSUPPORTED
     # weight packing: host-side checks before any launch
     pk = archer.lib.archer_pack_weight
     a0, a1 = C.c_void_p(1 << 20), C.c_void_p(1 << 30)

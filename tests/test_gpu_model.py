@@ -291,7 +291,8 @@ def test_full_width_two_layer_llada_shape(gateup_fp16):
 @pytest.mark.parametrize("gateup_fp16", [True, False])
 def test_full_width_two_layer_llada_long_prompt(gateup_fp16):
     """d 4096, 32 heads x 128, F 12288, vocab 126464, P 4096, G 256 (two layers); the
-    4352-row refresh runs 128 x 256 gate/up tiles, fp16 or two-term."""
+    4352-row refresh runs QKV and gate/up (fp16 or two-term) as 4096 rows of 256 x 256 tiles and 256 rows apart, O
+    and down as 4096 rows of folded 128 x 256 tiles and 256 in slices."""
     import time
     w = get_workload("llada_p4096")
     m = dataclasses.replace(w.model, n_layers=2, gateup_fp16=gateup_fp16)
