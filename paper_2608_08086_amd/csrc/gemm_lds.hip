@@ -212,9 +212,6 @@ __global__ __launch_bounds__(512, 1) void gemm_lds_kernel(GemmArgs a) {
   // faster (LLaDA-8B gate/up and QKV shapes at 256 and 768 rows), 128 x 128
   // tiles 0-3 %, bitwise the same.
   constexpr bool ROLL = NA == 2 && (CB == 4 || CB == 6 || CB == 8) && !FOLD;
-  // Two-term tiles of 32 columns per wave: two fragment sets, the reads of
-  // tile g + 1 spread one per lo-term MFMA of tile g.
-  constexpr bool PIPE = NA == 2 && CB <= 4 && !FOLD && !ROLL;
   // Single-term tiles (except folded): the MFMAs of the first half of the
   // weight blocks of tile g run before X_g, those of the second half after
   // it.  After X_g the weight fragments of the first half are refilled with
@@ -313,34 +310,15 @@ __global__ __launch_bounds__(512, 1) void gemm_lds_kernel(GemmArgs a) {
       }
     }
   };
+  // folded slices: two fragment sets, the next tile's read between the terms
   auto tile_body = [&](int g, int cur) {
     mfma_term(cur, 0);
-    if constexpr (PIPE) {
-      if (g + 1 < ntot) {
-        __builtin_amdgcn_s_waitcnt(GL_LGKMCNT0);   // this wave's reads of tile g are done
-        gl_barrier();                               // X_g
-        read_frags(g + 1, cur ^ 1);
-        mfma_term(cur, 1);
-        constexpr int NRD = CB + NA * RB, NM = RB * CB;
-#pragma unroll
-        for (int i = 0; i < (NRD < NM ? NRD : NM); ++i) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
-        }
-        if constexpr (NM > NRD) __builtin_amdgcn_sched_group_barrier(0x008, NM - NRD, 0);
-        if constexpr (NRD > NM) __builtin_amdgcn_sched_group_barrier(0x100, NRD - NM, 0);
-        __builtin_amdgcn_sched_barrier(0);
-      } else {
-        mfma_term(cur, 1);
-      }
-    } else {
-      if (g + 1 < ntot) {
-        __builtin_amdgcn_s_waitcnt(GL_LGKMCNT0);   // this wave's reads of tile g are done
-        gl_barrier();                               // X_g
-        read_frags(g + 1, cur ^ 1);
-      }
-      if constexpr (NA == 2) mfma_term(cur, 1);
+    if (g + 1 < ntot) {
+      __builtin_amdgcn_s_waitcnt(GL_LGKMCNT0);   // this wave's reads of tile g are done
+      gl_barrier();                               // X_g
+      read_frags(g + 1, cur ^ 1);
     }
+    if constexpr (NA == 2) mfma_term(cur, 1);
     if constexpr (FOLD) {
       if ((g + 1) % kt_slice == 0) {
 #pragma unroll
@@ -410,28 +388,30 @@ __global__ __launch_bounds__(512, 1) void gemm_lds_kernel(GemmArgs a) {
     tile_epilogue<BM, BN, WGN, RB, CB, EPI, STAGED, STATS, NST * STAGE, 512>(a, smem, tile_n, m0, wm, wn, lane, tid, tc, acc);
 }
 
-template <int BM, int BN, int WGM, int WGN, int NST, int EPI, int MODE>
+// The launches gemm_pick_cfg makes: 128 x 192 tiles run one slice of bf16 operands or separate
+// slices (fp16 operands of one slice have wide tiles, folded ones spill), 128 x 128 tiles all of them.
+template <int BN, int EPI, int MODE>
 void lds_mode(const GemmArgs& a, int grid, hipStream_t st) {
   if (a.f16) {
-    if constexpr (EPI == EPI_SWIGLU) gemm_lds_kernel<BM, BN, WGM, WGN, NST, EPI, false, MODE, true><<<grid, 512, 0, st>>>(a);
+    if constexpr (EPI == EPI_SWIGLU && (BN == 128 || MODE == 2))
+      gemm_lds_kernel<128, BN, 2, 2, 4, EPI, false, MODE, true><<<grid, 512, 0, st>>>(a);
   } else if (a.A2) {
-    gemm_lds_kernel<BM, BN, WGM, WGN, NST, EPI, true, MODE><<<grid, 512, 0, st>>>(a);
+    gemm_lds_kernel<128, BN, 2, 2, 4, EPI, true, MODE><<<grid, 512, 0, st>>>(a);
   } else {
-    gemm_lds_kernel<BM, BN, WGM, WGN, NST, EPI, false, MODE><<<grid, 512, 0, st>>>(a);
+    gemm_lds_kernel<128, BN, 2, 2, 4, EPI, false, MODE><<<grid, 512, 0, st>>>(a);
   }
 }
 
-template <int BM, int BN, int WGM, int WGN, int NST, int EPI>
+template <int BN, int EPI>
 void lds_cfg(const GemmArgs& a, bool partial, hipStream_t st) {
-  const int n_tiles = a.N / BN, m_tiles = (a.M + BM - 1) / BM;
-  const int grid = gemm_grid_size(n_tiles, m_tiles, partial ? a.ksplit : 1);
+  const int grid = gemm_grid_size(a.N / BN, (a.M + 127) / 128, partial ? a.ksplit : 1);
   if (partial) {
-    lds_mode<BM, BN, WGM, WGN, NST, EPI, 2>(a, grid, st);
+    lds_mode<BN, EPI, 2>(a, grid, st);
     launch_gemm_reduce(EPI, a, st);
   } else if (a.ksplit > 1) {
-    lds_mode<BM, BN, WGM, WGN, NST, EPI, 1>(a, grid, st);
+    if constexpr (BN == 128) lds_mode<BN, EPI, 1>(a, grid, st);
   } else {
-    lds_mode<BM, BN, WGM, WGN, NST, EPI, 0>(a, grid, st);
+    lds_mode<BN, EPI, 0>(a, grid, st);
   }
 }
 
@@ -467,8 +447,8 @@ void lds_rows64(const GemmArgs& a, bool partial, hipStream_t st) {
 template <int EPI>
 void lds_epi(int c, const GemmArgs& a, bool partial, hipStream_t st) {
   switch (c) {
-    case 0: lds_cfg<128, 192, 2, 2, 4, EPI>(a, partial, st); break;
-    case 1: lds_cfg<128, 128, 2, 2, 4, EPI>(a, partial, st); break;
+    case 0: lds_cfg<192, EPI>(a, partial, st); break;
+    case 1: lds_cfg<128, EPI>(a, partial, st); break;
     case 3: lds_rows64<192, EPI>(a, partial, st); break;
     case 4: lds_rows64<128, EPI>(a, partial, st); break;
     default: {
@@ -509,14 +489,10 @@ bool gemm_lds_cfg_ok(int c, const GemmArgs& a) {
   return true;
 }
 
-int gemm_lds_tiles(int c, const GemmArgs& a) {
-  const LdsCfg& k = kLds[c];
-  return (a.N / k.BN) * ((a.M + k.BM - 1) / k.BM);
-}
-
 int launch_gemm_lds_cfg(int epi, int c, bool partial, const GemmArgs& a, hipStream_t st) {
   if (!gemm_args_ok(epi, a) || !gemm_lds_cfg_ok(c, a)) return 1;
   if (partial && (!a.part || a.ksplit < 2)) return 1;
+  if (c == 0 && !partial && (a.ksplit != 1 || a.f16)) return 1;
   if (c == 2 && !a.A2 && epi != EPI_STORE) return 1;
   if (c >= 3 && !partial && (a.ksplit != 1 || a.tstat)) return 1;
   switch (epi) {

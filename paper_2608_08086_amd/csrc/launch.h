@@ -124,7 +124,6 @@ bool gemm_wide_ok(int c, const GemmArgs& a, int epi);
 int launch_gemm_wide(int epi, int c, const GemmArgs& a, hipStream_t st);
 int gemm_ksplit(int N, int K, int rows);
 bool gemm_lds_cfg_ok(int c, const GemmArgs& a);
-int gemm_lds_tiles(int c, const GemmArgs& a);
 int launch_gemm_lds_cfg(int epi, int c, bool partial, const GemmArgs& a, hipStream_t st);
 void launch_gemm_reduce(int epi, const GemmArgs& a, hipStream_t st);
 int gemm_grid_size(int n_tiles, int m_tiles, int S);
