@@ -494,15 +494,17 @@ static bool use_partials(const GemmArgs& a) { return a.ksplit > 1 && a.part && a
 // round of 256 workgroups (one per CU) a part that grows with k and TILE_US of
 // filling and draining.  Two-term bf16 and single-term fp16 launches; 0: not a
 // configuration of the kind.  Fitted to the LLaDA-8B and Dream-7B projections at 64
-// to 2048 rows and to the ragged batch's 4096- and 24853-row passes.  Two
+// to 2048 rows and to the ragged batch's 4096- and 24853-row passes; of 28 launches
+// of other shapes (65 to 4300 rows, N 2048 to 30000, K 1024 to 16000) the tile with the
+// least time was also the fastest in 22, five lost 3 to 9 % and one 17.  Two
 // workgroups of the 64-row tiles share a CU: further rounds cost less than the
 // first, and only one fill and drain shows (LLaDA-8B QKV in 64 x 192 tiles: 50 us
 // for 1 round, 124 for 3, 311 for 8; O at 1024 rows in 4 slices: 64 x 128 tiles
 // 84 us, 128 x 128 91).  A partly filled last round of 128 x 256 tiles is faster than
 // a full one (down of the Dream-7B shape, K 18944: 140 workgroups 326 us, 168 345,
-// 224 386); the other tiles showed no such gain.  Folded slices (all of K in a tile,
-// in parts) cost FOLD_US a round: down of the LLaDA-8B shape, 4 slices, 335 us a round,
-// O 131.
+// 224 386, the only shape behind the 0.7 and 0.3); the other tiles showed no such
+// gain.  Folded slices (all of K in a tile, in parts) cost FOLD_US a round: down of
+// the LLaDA-8B shape, 4 slices, 335 us a round, O 131.
 static double tiles_us(int cfg, bool f16, int grid, double k) {
   const int rounds = (grid + 255) / 256;
   constexpr double TILE_US = 5.0, FOLD_US = 20.0;

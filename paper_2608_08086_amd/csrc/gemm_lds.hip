@@ -424,9 +424,11 @@ const LdsCfg kLds[GEMM_NCFG_LDS] = {
     {64, 128},    // 4: 2 x 2 multiply waves of 32 x 64, 4 stages, two-term
 };
 
-// 64-row tiles, for launches of few rows.  A workgroup of the small tiles gets
-// about 60 bytes per ns into its LDS, however many CUs run and however many
-// stages are in flight (4 and 7 alike), so a k step of a two-term launch costs
+// 64-row tiles, for launches of few rows.  A workgroup of the small tiles was seen
+// to get about 60 bytes per ns into its LDS, however many CUs run and however many
+// stages are in flight (4 and 7 alike); why no more is not known (28 bytes per clock;
+// texture-data and address units 75 and 70 % busy, matrix cores 41, LDS 17 at 256
+// rows).  At that rate a k step of a two-term launch costs
 // (2 BM + BN) x 64 bytes: beside two activation terms a row costs twice a
 // column, and 64 x 192 loads 20 KB where 128 x 128 loads 24 KB for 4 / 3 of the
 // products.  LLaDA-8B QKV at 256 rows (256 workgroups against 192) 55 -> 50 us,

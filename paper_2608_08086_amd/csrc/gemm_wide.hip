@@ -2,16 +2,18 @@
 // multiply, so that a wave has the SIMD's whole register file (a 128 x 128 wave
 // tile: 256 accumulation registers for the sums, up to 256 others).
 //
-// What bounds these GEMMs is the LDS port.  A direct load writes 64 bytes of
-// LDS per clock and a fragment read takes 128, so a k step of 32 costs
-//   (read bytes) / 128 + (loaded bytes) / 64 clocks
-// beside its MFMAs.  fp16 operands, per 256 x 256 of output: 128 x 256 tiles of
-// 64 x 128 wave tiles (gemm_lds.hip) need 1536 clocks of LDS for 1024 of MFMA,
-// 256 x 256 tiles of 128 x 128 wave tiles 1024.  Measured on the LLaDA-8B gate/up
-// shape: 4096 rows 745-790 -> 607-641 us, 24853 rows 4540 -> 3680 us (1.36
-// PFLOP/s; the loop without any load runs at 1.6, where random operands hold
-// the clock down).  Two-term bf16 operands need 2048 clocks of MFMA for 1536
-// of LDS, so they gain less: 4096 rows, down 557 -> 522 us, O 201 -> 189.
+// What bounds the fp16 tiles is the path of the direct loads into LDS: the
+// texture-data unit they pass through is busy 93 % of the cycles, the matrix
+// cores 66 % and the LDS itself 17 % (54 % and 20 % in the 128 x 256 tiles of
+// gemm_lds.hip, texture data the same).  Loads move about 23 bytes per busy clock
+// and CU there, so the tile that loads least per product wins: per 256 x 256 of
+// output and k step of 32, tiles of 128 x 256 load 48 KB, of 256 x 256 32 KB.  Measured
+// on the LLaDA-8B gate/up shape: 4096 rows 745-790 -> 607-641 us, 24853 rows
+// 4540 -> 3680 us (1.36 PFLOP/s; the loop without any load runs at 1.6, where
+// random operands hold the clock down).  Two-term bf16 operands take twice the
+// MFMAs for half as much again of loads: matrix cores 68-76 % busy, texture data
+// 64-72 %, at a clock of 2.0 GHz; they gain less: 4096 rows, down 557 -> 522 us,
+// O 201 -> 189.
 //
 // Two-term steps: the lo fragments of tile g are read among its hi-term MFMAs;
 // then the barrier; then, among the lo-term MFMAs, the weight and hi fragments
