@@ -181,6 +181,12 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& a, char* smem, int
         const int r = wm * WM + rb * 16 + lc, row = m0 + r;
         if (row >= a.M) continue;
         const float2* cs = a.rope + (size_t)a.row_pos[row] * half;
+        // a row's angles are all requested before the first is used
+        float2 ang[CB / 2][4];
+#pragma unroll
+        for (int cb = 0; cb < CB / 2; ++cb)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) ang[cb][e] = cs[(tc[cb] - lc + 4 * lg) % half + e];
 #pragma unroll
         for (int cb = 0; cb < CB / 2; ++cb) {
           const int c = tc[cb] - lc + 4 * lg, j = c % half;
@@ -189,7 +195,7 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& a, char* smem, int
           f32x4 v1 = acc[rb][cb], v2 = acc[rb][cb + CB / 2];
           asm volatile("" : "+v"(v1), "+v"(v2));
           f16x4 o1, o2;
-          rope_rotate4(v1, v2, cs + j, &o1, &o2);
+          rope_rotate4(v1, v2, ang[cb], &o1, &o2);
           *(f16x4*)q = o1;
           *(f16x4*)(q + half) = o2;
         }

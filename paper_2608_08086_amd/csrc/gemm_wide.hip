@@ -25,8 +25,9 @@
 //
 // FOLD tiles run the K slices of a split context one after the other, 128 x 256 so
 // that a second set of sums, the running total, fits beside the accumulators: the
-// bits of separate slices without their partial planes, for 112 us per 256 tiles
-// and K 4096 against 75 in half a 256 x 256 tile (gemm_split_rows says where).
+// bits of separate slices without their partial planes, for 112 to 131 us per 256
+// tiles and K 4096 where half a round of 256 x 256 tiles takes 100 to 113
+// (gemm_split_rows says where).
 //
 // Addressing, stage layout and epilogues are those of gemm_lds.hip, and so are
 // the k order and the bits of every result.
@@ -251,7 +252,7 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(GemmArgs a) {
   for (int cb = 0; cb < CB; ++cb) tc[cb] = tcol(cb) + t0;
   // 256 x 256 QKV tiles leave no registers for the element-wise stores of a tile
   // that straddles the value heads: only launches without such tiles take them
-  // (and even so two registers go through scratch memory between the loop and the stores)
+  // (and even so three registers go through scratch memory between the loop and the stores)
   constexpr bool QKV = EPI == EPI_QKV, ONLY_STAGED = BM * BN == 65536;
   if constexpr (FOLD)
     tile_epilogue<BM, BN, WGN, RB, CB, EPI, QKV, false, NST * STAGE, 256, ONLY_STAGED>(a, smem, tile_n, m0, wm, wn, lane,
