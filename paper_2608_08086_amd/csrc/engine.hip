@@ -192,6 +192,7 @@ struct archer_ctx {
     int T = 0, t = 0;          // decisions in the schedule / made so far
     int cur = 0;               // g buffer (gbuf0 / gbuf1) holding the current response
     bool keep = true;          // forwards store their logits in the workspace
+    bool lost = false;         // an archer_decide has overwritten the partials of the last forward (kept logits remain)
     int r[ARCHER_MAXB] = {0};  // step of each sequence's anchor
   } ses;
   // timing
@@ -500,18 +501,20 @@ archer_status run_forward(archer_ctx* c, bool full, const std::vector<int>& sel,
 }
 
 // fused: the partials of these logits were written by the LM head of the
-// forward that produced them (same bits as the stand-alone kernel would give)
+// forward that produced them (same bits as the stand-alone kernel would give).
+// aside: the workspace offset of other scratch for the partials, or 0
 archer_status decide_impl(archer_ctx* c, const float* logits, const int32_t* g_in, int32_t* g_out, int k,
                           float tau, int max_remask, int final_step, int32_t* dist, int32_t* unmask_pos,
                           int32_t* remask_pos, int32_t* tr_dist, int32_t* tr_unmask, int32_t* tr_utok,
-                          int32_t* tr_remask, bool fused = false) {
+                          int32_t* tr_remask, bool fused = false, size_t aside = 0) {
   const int B = c->batch, G = c->lim.resp_len, V = c->cfg.vocab;
   const int rows = B * G;
   const float log_tau = (float)std::log((double)tau);
   const Layout& L = c->L;
-  float2* tstat = c->at<float2>(L.tstat);
-  int* targ = c->at<int>(L.targ);
-  float* zg = c->at<float>(L.zg);
+  const size_t np = (size_t)rows * c->np;
+  float2* tstat = c->at<float2>(aside ? aside : L.tstat);
+  int* targ = aside ? (int*)(tstat + np) : c->at<int>(L.targ);
+  float* zg = aside ? (float*)(targ + np) : c->at<float>(L.zg);
   return timed(c, ARCHER_K_DECIDE, fused ? (double)rows * c->np * 12 : (double)rows * V * 4, 0.0, [&] {
     if (!fused) launch_tile_stats(rows, logits, V, c->stat_tile, c->np, c->cfg.mask_id, g_in, tstat, targ, zg,
                                   c->stream);
@@ -657,7 +660,7 @@ void fill_header(const archer_ctx* c, SnapHeader& h) {
   h.T = c->ses.T;
   h.t = c->ses.t;
   h.cur = c->ses.cur;
-  h.keep = c->ses.keep ? 1 : 0;
+  h.keep = (c->ses.keep ? 1 : 0) | (c->ses.lost ? 2 : 0);
 }
 
 }  // namespace
@@ -773,10 +776,15 @@ archer_status archer_decide(archer_ctx* c, const float* logits, const int32_t* g
   if (dc->unmask_per_step < 1 || dc->unmask_per_step > c->lim.resp_len) return fail(ARCHER_E_ARG, "unmask_per_step outside [1, G]");
   if (!(dc->remask_threshold > 0.f && dc->remask_threshold < 1.f)) return fail(ARCHER_E_ARG, "remask_threshold outside (0, 1)");
   if (dc->max_remask != 0 && dc->max_remask != 1) return fail(ARCHER_E_ARG, "max_remask must be 0 or 1");
+  // A session's next decision reads the partials that its last forward wrote.  The
+  // logits buffer of a session that keeps no logits is free for this call's (12 c->np + 4
+  // bytes per row of 4 vocab); one that keeps them reads those instead.
+  const bool live = c->ses.active && c->stat_fused;
   archer_status st = decide_impl(c, logits, g_in, g_out, dc->unmask_per_step, dc->remask_threshold, dc->max_remask,
                                  dc->final_step, dist_out, unmask_pos, remask_pos, nullptr, nullptr, nullptr,
-                                 nullptr);
+                                 nullptr, false, live && !c->ses.keep ? c->L.logits : 0);
   if (st) return st;
+  if (live && c->ses.keep) c->ses.lost = true;
   HIPCHK(hipGetLastError());
   return ARCHER_OK;
 }
@@ -799,6 +807,7 @@ archer_status archer_session_begin(archer_ctx* c, int32_t batch, const int32_t* 
   S.t = 0;
   S.cur = 0;
   S.keep = dc->keep_logits != 0 || !c->stat_fused;
+  S.lost = false;
   for (int b = 0; b < ARCHER_MAXB; ++b) S.r[b] = 0;
   int* g0 = c->at<int>(c->L.gbuf0);
   HIPCHK(hipMemcpyAsync(g0, response_init, (size_t)B * G * 4, hipMemcpyDeviceToDevice, c->stream));
@@ -837,7 +846,7 @@ archer_status archer_session_advance(archer_ctx* c, int32_t n, int32_t first_for
     int32_t* trt = tr.unmask_tok ? tr.unmask_tok + (size_t)t * B * k : nullptr;
     int32_t* trr = tr.remask_pos ? tr.remask_pos + (size_t)t * B : nullptr;
     st = decide_impl(c, logits, g[S.cur], g[S.cur ^ 1], k, S.cfg.remask_threshold, S.cfg.max_remask,
-                     final ? 1 : 0, nullptr, nullptr, nullptr, trd, tru, trt, trr, c->stat_fused);
+                     final ? 1 : 0, nullptr, nullptr, nullptr, trd, tru, trt, trr, c->stat_fused && !S.lost);
     if (st) return st;
     S.cur ^= 1;
     S.t = t + 1;
@@ -867,6 +876,7 @@ archer_status archer_session_advance(archer_ctx* c, int32_t n, int32_t first_for
                       tr.age ? tr.age + (size_t)s * B : nullptr, ref_row, age_row, B, c->stream);
     if ((st = run_forward(c, true, full, S.prompt, g[S.cur], logits, true))) return st;
     if ((st = run_forward(c, false, cached, nullptr, g[S.cur], logits, true))) return st;
+    S.lost = false;
   }
   HIPCHK(hipGetLastError());
   if (t_out) *t_out = S.t;
@@ -929,7 +939,8 @@ archer_status archer_session_restore(archer_ctx* c, const void* src, size_t byte
   c->ses.T = h.T;
   c->ses.t = h.t;
   c->ses.cur = h.cur;
-  c->ses.keep = h.keep != 0;
+  c->ses.keep = (h.keep & 1) != 0;
+  c->ses.lost = (h.keep & 2) != 0;
   const char* s = (const char*)src;
   for (const SnapRegion& r : snapshot_regions(c))
     HIPCHK(hipMemcpyAsync(c->ws + r.ws_off, s + r.snap_off, r.bytes, hipMemcpyDeviceToDevice, c->stream));

@@ -85,6 +85,36 @@ def test_decode_equals_session_advanced_in_pieces(kind):
     ctx.sync()
 
 
+@pytest.mark.parametrize("keep", [False, True])
+def test_decide_between_advances_leaves_the_session_intact(keep):
+    """archer_decide on other logits while a session with fused statistics is active: the session's
+    next decisions are those of an undisturbed one, from a snapshot taken then as well."""
+    a = archer()
+    m, W, lens, ps = _bf16_batch()
+    G, T, B = 32, 12, 3
+    say(f"decide between advances, keep_logits={keep}")
+    ctx = make_ctx(m, W, B, max(lens), sum(lens), G)
+    prompt = dev_i32(np.concatenate(ps))
+    g0 = np.full((B, G), m.mask_id, np.int32)
+    kw = dict(policy=a.AGE, K=4, steps=T, k=1, tau=0.1, keep_logits=keep)
+    out, tr = ctx.decode(prompt, lens, dev_i32(g0), **kw)
+    z = torch.randn(B, G, m.vocab, device="cuda", generator=torch.Generator(device="cuda").manual_seed(3))
+    tr2 = ctx.session_begin(prompt, lens, dev_i32(g0), **kw)
+    want = None
+    for t in range(T):
+        for _ in range(2):
+            g, _, um, rm = ctx.decide(z, dev_i32(g0), k=2)   # the distance is to the session's anchor, which moves
+            other = [g, um, rm]
+            want = want or other
+            assert all(bool((x == y).all()) for x, y in zip(other, want))
+        if t == 5:
+            ctx.session_restore(ctx.session_save())
+        assert ctx.session_advance(1) == t + 1
+    _same_trace(tr, tr2)
+    assert bool((ctx.session_response() == out).all())
+
+
+
 def test_snapshot_restore_replays_bitwise():
     a = archer()
     m, W, lens, ps = _bf16_batch()
