@@ -61,10 +61,10 @@ def test_gemm_f32_tiles_match_oracle(M, N, K):
                                    (2600, 4608, 192)])
 def test_gemm_two_term_activation_matches_oracle(M, N, K):
     """A = hi + lo (bf16 pair of an fp32 activation) against the unrounded activation; N 65536
-    runs the 128 x 256 tiles (enough column tiles), with a ragged last row tile.  3900 x 4096
-    (16 column tiles of 256, 31 row tiles) and 2600 x 4608 (24 column tiles of 192, 21 row
-    tiles) have few column tiles and many row tiles, so their row tiles are split over 4 and 2
-    XCDs per column-tile set, in shares of unequal size."""
+    has many column tiles (64 x 128 at this K), with a ragged last row tile.  3900 x 4096 (16
+    column tiles of 256, 16 row tiles of 256) and 2600 x 4608 (24 column tiles of 192, 41 row
+    tiles of 64) have few column tiles and many row tiles, so their row tiles are split over 4
+    and 2 XCDs per column-tile set, the latter in shares of unequal size."""
     say(f"gemm two-term bf16 M={M} N={N} K={K}")
     a = archer()
     import torch

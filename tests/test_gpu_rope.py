@@ -10,7 +10,7 @@ enough to show in each of these caches.
 import numpy as np
 import pytest
 
-from gpu_util import dev_i32, make_ctx, say
+from gpu_util import archer, dev_i32, make_ctx, say
 from synth.gen import bf16_bits_to_f32, f32_to_bf16_bits, model_weights
 from synth.workloads import ModelShape
 
@@ -34,20 +34,24 @@ def _expected_k(W, m, tokens, gain):
     return k.transpose(1, 0, 2)
 
 
-@pytest.mark.parametrize("d,hq,hkv,hd,B,P,G", [
-    (1024, 3, 1, 64, 1, 4000, 64),      # 320 columns: register-staged kernel
-    (256, 4, 2, 64, 1, 3000, 64),       # K in slices of separate workgroups, reduced
-    (256, 4, 2, 64, 1, 4700, 64),       # more rows than the partial buffer: slices folded in a workgroup
-    (256, 8, 8, 128, 8, 100, 256),      # one slice, few rows
-    (256, 32, 32, 128, 8, 300, 256),    # one slice, 4448 rows
-    (1024, 32, 32, 128, 16, 256, 256),  # one slice, 8192 rows
-    (1024, 28, 4, 128, 16, 256, 256),   # grouped queries
-    (1024, 36, 4, 64, 16, 256, 256),    # tiles that straddle the key and value heads
+@pytest.mark.parametrize("d,hq,hkv,hd,B,P,G,tiles", [
+    (1024, 3, 1, 64, 1, 4000, 64, "4064 rows staged 256x64, 8 slices"),
+    (256, 4, 2, 64, 1, 3000, 64, "3064 rows 64x128, 4 slices"),
+    (256, 4, 2, 64, 1, 4700, 64, "4764 rows 128x128, 4 folded slices"),
+    (256, 8, 8, 128, 8, 100, 256, "2848 rows 64x192"),
+    (256, 32, 32, 128, 8, 300, 256, "4448 rows 64x192"),
+    (1024, 32, 32, 128, 16, 256, 256, "8192 rows wide 256x256"),
+    (1024, 28, 4, 128, 16, 256, 256, "8192 rows wide 256x192"),   # tiles that straddle the key and value heads
+    (1024, 42, 3, 64, 16, 256, 256, "8192 rows wide 256x192"),
+    (1024, 36, 4, 64, 16, 256, 256, "8192 rows 128x256"),
+    (1024, 10, 5, 128, 3, 1390, 72, "3072 rows wide 128x256, 8 folded slices; 1314 rows 64x128, 8 slices"),
 ])
-def test_stored_keys_are_rounded_once(d, hq, hkv, hd, B, P, G):
+def test_stored_keys_are_rounded_once(d, hq, hkv, hd, B, P, G, tiles):
     say(f"rope d={d} heads={hq}/{hkv}x{hd} B={B} P={P} G={G}")
     m = ModelShape(n_layers=1, d_model=d, n_heads=hq, n_kv_heads=hkv, head_dim=hd, d_ff=128, vocab=1024, dtype="bf16",
                    init_std=0.05)
+    a = archer()
+    assert a.projection_tiles(m, (B, P, B * P, G), a.K_GEMM_QKV, B * (P + G)) == tiles
     W = model_weights(m, seed=21)
     emb = np.zeros((m.vocab, d), np.float32)
     emb[np.arange(m.vocab), np.arange(m.vocab) % d] = 2.0**20    # its square swamps the norm's epsilon
